@@ -48,8 +48,7 @@ namespace {
 constexpr int kGreedyPasses = 32;   // visits of a blocked position in the round after the grid rounds
 constexpr int kTile = 256;      // similarity tile of the bf16 path (GramGemm)
 constexpr int kTileF32 = 64;    // similarity tile of the fp32 path
-constexpr int kGroupsF32 = kTileF32 / 16;   // 16-column bit groups per tile row
-constexpr int kWordsF32 = kTileF32 / 64;    // bitmask words per tile row
+constexpr int kGramF32Blocks = 3;   // its blocks a CU (48 KB of operand ring each)
 constexpr int kStateUndecided = 0, kStateKept = 1, kStateAbsorbed = 2;
 constexpr int kTileQueues = 8;  // tile queues of the history similarity kernel, one per XCD
 
@@ -279,31 +278,51 @@ __device__ __forceinline__ TileCoord decode_tile(int tile, const int32_t* __rest
   return c;
 }
 
-// Writes the tile's adjacency words: rows of tile-row ti at words
-// kWordsF32 * tj + w (from dbits) and, off the diagonal, rows of tile-row tj
-// at words kWordsF32 * ti + w (from tbits).  dbits/tbits: [kTileF32 rows]
-// [kGroupsF32 groups of 16 columns].
-__device__ __forceinline__ void write_tile_words(const TileCoord& c, const uint16_t (*dbits)[kGroupsF32],
-                                                 const uint16_t (*tbits)[kGroupsF32],
+// v_writelane_b32: `old` with lane `lane` replaced by the wave-uniform
+// `value` (the LLVM intrinsic, which clang does not expose as a builtin).
+__device__ int amdgcn_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane");
+
+// Writes the words of one predicate of a 64 x 64 tile: row rl of tile-row ti
+// at word tj (dw[rl]) and, off the diagonal, row rl of tile-row tj at word ti
+// (tw[rl], the transposed tile).  A 64-column tile is one word.
+__device__ __forceinline__ void write_tile_words(const TileCoord& c, const uint64_t* dw, const uint64_t* tw,
                                                  uint64_t* __restrict__ bitmask, long long base) {
   const int tid = threadIdx.x;
-  if (tid >= kTileF32 * kWordsF32) return;
-  const int rl = tid / kWordsF32, ww = tid % kWordsF32;
-  auto pack = [](const uint16_t* g) {
-    return static_cast<uint64_t>(g[0]) | (static_cast<uint64_t>(g[1]) << 16) |
-           (static_cast<uint64_t>(g[2]) << 32) | (static_cast<uint64_t>(g[3]) << 48);
-  };
-  {
-    const int a = c.ti * kTileF32 + rl;
-    const int wd = kWordsF32 * c.tj + ww;
-    if (a < c.n && wd < c.W)
-      bitmask[base + static_cast<long long>(a) * c.W + wd] = pack(&dbits[rl][4 * ww]);
-  }
-  if (c.ti != c.tj) {
-    const int b = c.tj * kTileF32 + rl;
-    const int wd = kWordsF32 * c.ti + ww;
-    if (b < c.n && wd < c.W)
-      bitmask[base + static_cast<long long>(b) * c.W + wd] = pack(&tbits[rl][4 * ww]);
+  if (tid >= 2 * kTileF32) return;
+  const bool mirror = tid >= kTileF32;
+  if (mirror && c.ti == c.tj) return;
+  const int rl = mirror ? tid - kTileF32 : tid;
+  const int a = (mirror ? c.tj : c.ti) * kTileF32 + rl;
+  if (a < c.n) bitmask[base + static_cast<long long>(a) * c.W + (mirror ? c.ti : c.tj)] = mirror ? tw[rl] : dw[rl];
+}
+
+// Bit pieces of NM predicates (bit m of pr[v]) over one 32 x 32 block in the
+// accumulator layout (lane l: column l % 32, value v: row 8 (v / 4) + v % 4 +
+// 4 (l / 32)): row pieces (32 columns) and column pieces (32 rows) of the
+// predicates, stored by lanes 0-31 at d[m][rrow][cb] and t[m][col][rb] (32-bit
+// halves of 64-bit words).
+template <int NM>
+__device__ __forceinline__ void block_bits(const uint32_t (&pr)[16], uint32_t* d, uint32_t* t, int rrow0, int col0) {
+  const int lane = threadIdx.x & 63, l31 = lane & 31, hi = lane >> 5;
+#pragma unroll
+  for (int m = 0; m < NM; ++m) {
+    int piece = 0;
+    uint32_t col = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int rv = 8 * (v >> 2) + (v & 3);
+      const bool p = (pr[v] >> m) & 1u;
+      const uint64_t bm = __ballot(p);
+      piece = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(bm)), rv, piece);
+      piece = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(bm >> 32)), rv + 4, piece);
+      col |= p ? 1u << rv : 0u;
+    }
+    col <<= 4 * hi;
+    col |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(col), 32, 64));
+    if (lane < 32) {
+      d[(m * kTileF32 + rrow0 + l31) * 2 + (col0 >> 5)] = static_cast<uint32_t>(piece);
+      t[(m * kTileF32 + col0 + l31) * 2 + (rrow0 >> 5)] = col;
+    }
   }
 }
 
@@ -343,10 +362,6 @@ __device__ __forceinline__ TileCoord decode_tile_grouped(int tile, const int32_t
   bucket_lookup_loads(tile_off, offsets, E, to, o0, o1);
   return decode_tile_grouped_from(tile, to, o0, o1, E);
 }
-
-// v_writelane_b32: `old` with lane `lane` replaced by the wave-uniform
-// `value` (the LLVM intrinsic, which clang does not expose as a builtin).
-__device__ int amdgcn_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane");
 
 using GramGemm = GemmBig64;
 static_assert(GramGemm::BM == kTile && GramGemm::BN == kTile, "similarity tile");
@@ -726,115 +741,6 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
     item = nitem;
     tile = next;
     c = cn;
-  }
-}
-
-// float32 tokens: 64-row tiles (small buckets give more tiles than with the
-// bf16 path's 256), same bitmask, plain FMA with a 4x4 micro-tile per
-// thread.
-__global__ __launch_bounds__(256) void gram_kernel_f32(
-    const float* __restrict__ X, int d, const int32_t* __restrict__ perm_token,
-    const int32_t* __restrict__ offsets, int E, const float* __restrict__ inv_norm, float h,
-    const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off,
-    const int* __restrict__ err, uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg) {
-  constexpr int KC = 16;
-  __shared__ float Ps[kTileF32][KC + 1];
-  __shared__ float Qs[kTileF32][KC + 1];
-  constexpr int MT = kTileF32 / 16;   // micro-tile edge: 16 x 16 threads cover the tile
-  __shared__ uint8_t edge[kTileF32][kTileF32];
-  __shared__ uint16_t dbits[kTileF32][kGroupsF32];
-  __shared__ uint16_t tbits[kTileF32][kGroupsF32];
-  __shared__ float inv_a[kTileF32], inv_b[kTileF32];
-  if (*err) return;
-  const int tid = threadIdx.x;
-  const int rb = (tid >> 4) * MT, cb = (tid & 15) * MT;
-  const int total = tile_off[E];
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    const TileCoord c = decode_tile(tile, tile_off, offsets, E);
-    const int32_t* pt = perm_token + c.lo;
-    if (tid < kTileF32) inv_a[tid] = inv_norm[pt[min(c.ti * kTileF32 + tid, c.n - 1)]];
-    else if (tid < 2 * kTileF32) inv_b[tid - kTileF32] = inv_norm[pt[min(c.tj * kTileF32 + tid - kTileF32, c.n - 1)]];
-    // staged element i of this thread: tile row r0 + 16i, column kk; the
-    // token rows are looked up once per tile and the next chunk is loaded
-    // into registers while the current one is multiplied
-    constexpr int PER = kTileF32 * KC / 256;
-    const int kk = tid % KC, r0 = tid / KC;
-    const float* pp[PER];
-    const float* qp[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int r = r0 + (256 / KC) * i;
-      pp[i] = X + static_cast<size_t>(pt[min(c.ti * kTileF32 + r, c.n - 1)]) * d + kk;
-      qp[i] = X + static_cast<size_t>(pt[min(c.tj * kTileF32 + r, c.n - 1)]) * d + kk;
-    }
-    float vp[PER], vq[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      vp[i] = pp[i][0];
-      vq[i] = qp[i][0];
-    }
-    float acc[MT][MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < MT; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < d; k0 += KC) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        Ps[r0 + (256 / KC) * i][kk] = vp[i];
-        Qs[r0 + (256 / KC) * i][kk] = vq[i];
-      }
-      __syncthreads();
-      if (k0 + KC < d) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          vp[i] = pp[i][k0 + KC];
-          vq[i] = qp[i][k0 + KC];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < KC; ++k) {
-        float pa[MT], qb[MT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) pa[i] = Ps[rb + i][k];
-#pragma unroll
-        for (int j = 0; j < MT; ++j) qb[j] = Qs[cb + j][k];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int j = 0; j < MT; ++j) acc[i][j] = fmaf(pa[i], qb[j], acc[i][j]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < MT; ++j) {
-        const int a = c.ti * kTileF32 + rb + i, b = c.tj * kTileF32 + cb + j;
-        const float cs = acc[i][j] * inv_a[rb + i] * inv_b[cb + j];
-        edge[rb + i][cb + j] = (a < c.n && b < c.n && a != b && cs >= h) ? 1 : 0;
-      }
-    __syncthreads();
-    for (int idx = tid; idx < kTileF32 * kGroupsF32; idx += 256) {
-      const int r = idx / kGroupsF32, g = idx % kGroupsF32;
-      uint32_t dv = 0, tv = 0;
-      for (int bit = 0; bit < 16; ++bit) {
-        dv |= static_cast<uint32_t>(edge[r][16 * g + bit]) << bit;
-        tv |= static_cast<uint32_t>(edge[16 * g + bit][r]) << bit;
-      }
-      dbits[r][g] = static_cast<uint16_t>(dv);
-      tbits[r][g] = static_cast<uint16_t>(tv);
-    }
-    __syncthreads();
-    if (tid < 2 * kTileF32) {
-      const bool mirror = tid >= kTileF32;
-      const int rl = mirror ? tid - kTileF32 : tid;
-      int cnt = 0;
-      for (int g = 0; g < kGroupsF32; ++g) cnt += __popc(mirror ? tbits[rl][g] : dbits[rl][g]);
-      const int r = (mirror ? c.tj : c.ti) * kTileF32 + rl;
-      if (cnt && r < c.n && (!mirror || c.ti != c.tj)) atomicAdd(&deg[c.lo + r], cnt);
-    }
-    write_tile_words(c, dbits, tbits, bitmask, bm_off[c.e]);
   }
 }
 
@@ -1312,148 +1218,107 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
   }
 }
 
-// float32 similarity with history: the 64-row tiles of gram_kernel_f32, every
-// tile computed; each pair takes weight 1 or 0 where the previous block
-// decided it and its cosine elsewhere; the record words are written beside
-// the adjacency words.
-template <bool HIN, bool HOUT>
-__global__ __launch_bounds__(256) void gram_hist_kernel_f32(
+// float32 similarity, with or without history (Sec. 5.1 step 2): 64 x 64
+// tiles on float32 MFMA (GemmF32; the products and sums are float32, as with
+// vector FMA, at twice its unpacked rate and without its LDS reads per
+// multiply-add).  Bound by the MFMA rate for large buckets, by a tile's
+// latency for small ones; three blocks a CU overlap one tile's loads and
+// epilogue with another's products.  On 8 buckets of about 750 rows
+// (d = 512): vector FMA tiles (4 x 4 a thread) 89 us, these 32 us; on 4 of 128
+// rows (d = 256): 23 and 10 us.
+// HIST: each pair takes weight 1 or 0 where the previous block decided it and
+// its cosine elsewhere (every tile computed); HOUT: the record words are
+// written beside the adjacency words.
+template <bool HIST, bool HIN, bool HOUT>
+__global__ __launch_bounds__(GemmF32::THREADS, kGramF32Blocks) void gram_kernel_f32(
     const float* __restrict__ X, int d, const int32_t* __restrict__ perm_token,
     const int32_t* __restrict__ offsets, int E, const float* __restrict__ inv_norm, HistParams hp,
     const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off,
     const int* __restrict__ err, uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg) {
-  constexpr int KC = 16;
+  using G = GemmF32;
+  static_assert(G::BM == kTileF32 && G::BN == kTileF32 && G::FM == 1 && G::FN == 1, "float32 similarity tile");
   constexpr int NM = HOUT ? 3 : 1;
-  __shared__ float Ps[kTileF32][KC + 1];
-  __shared__ float Qs[kTileF32][KC + 1];
-  constexpr int MT = kTileF32 / 16;
-  __shared__ uint8_t pred[kTileF32][kTileF32];   // bit m: predicate m of the pair
-  __shared__ uint16_t dbits[NM][kTileF32][kGroupsF32];
-  __shared__ uint16_t tbits[NM][kTileF32][kGroupsF32];
-  __shared__ float inv_a[kTileF32], inv_b[kTileF32];
-  __shared__ uint64_t rbw[2][kTileF32];
+  // one LDS array: the operand ring; the inverse norms of the tile's rows and
+  // columns; the predicates' words, direct and transposed; the previous
+  // classes of the tile's rows
+  constexpr int kInvOff = G::LDS_BYTES, kDOff = kInvOff + 2 * kTileF32 * 4, kTOff = kDOff + NM * kTileF32 * 8;
+  constexpr int kRbOff = kTOff + NM * kTileF32 * 8;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kRbOff + (HIN ? 2 * kTileF32 * 8 : 0)];
+  float* inv = reinterpret_cast<float*>(lds + kInvOff);
+  uint64_t* dw = reinterpret_cast<uint64_t*>(lds + kDOff);
+  uint64_t* tw = reinterpret_cast<uint64_t*>(lds + kTOff);
+  uint64_t* rbw = reinterpret_cast<uint64_t*>(lds + kRbOff);
   if (*err) return;
-  const int tid = threadIdx.x;
-  const int rb = (tid >> 4) * MT, cb = (tid & 15) * MT;
+  const int tid = threadIdx.x, lane = tid & 63, w = G::wave();
+  const int arow = G::wave_m(w) * 32, brow = G::wave_n(w) * 32;
+  const int l31 = lane & 31, hi = lane >> 5;
   const int total = tile_off[E];
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+  for (int tile = xcd_virtual_block(); tile < total; tile += gridDim.x) {
     const TileCoord c = decode_tile(tile, tile_off, offsets, E);
     const int32_t* pt = perm_token + c.lo;
     const long long bmo = bm_off[c.e];
-    if (tid < kTileF32) inv_a[tid] = inv_norm[pt[min(c.ti * kTileF32 + tid, c.n - 1)]];
-    else if (tid < 2 * kTileF32) inv_b[tid - kTileF32] = inv_norm[pt[min(c.tj * kTileF32 + tid - kTileF32, c.n - 1)]];
-    else if (tid < 3 * kTileF32) {
-      // previous classes: tile-row rows, word tj (64-column tiles are one word)
+    uint32_t poff[G::LP], qoff[G::LQ];
+#pragma unroll
+    for (int j = 0; j < G::LP; ++j)
+      poff[j] = static_cast<uint32_t>(pt[min(c.ti * kTileF32 + G::load_row(j), c.n - 1)]) * 2u * d;
+#pragma unroll
+    for (int j = 0; j < G::LQ; ++j)
+      qoff[j] = static_cast<uint32_t>(pt[min(c.tj * kTileF32 + G::load_row(G::LP + j) - G::BM, c.n - 1)]) * 2u * d;
+    if (tid < 2 * kTileF32) {
+      const int r = (tid < kTileF32 ? c.ti * kTileF32 : (c.tj - 1) * kTileF32) + tid;
+      inv[tid] = inv_norm[pt[min(r, c.n - 1)]];
+    } else if (HIN && tid < 3 * kTileF32) {
+      // previous classes: tile-row rows, word tj
       const int rl = tid - 2 * kTileF32, a = c.ti * kTileF32 + rl;
-      uint64_t h1 = 0, l1 = 0;
-      if constexpr (HIN) {
-        if (a < c.n) {
-          h1 = hp.rb_hi[bmo + static_cast<long long>(a) * c.W + c.tj];
-          l1 = hp.rb_lo[bmo + static_cast<long long>(a) * c.W + c.tj];
+      rbw[rl] = a < c.n ? hp.rb_hi[bmo + static_cast<long long>(a) * c.W + c.tj] : 0ull;
+      rbw[kTileF32 + rl] = a < c.n ? hp.rb_lo[bmo + static_cast<long long>(a) * c.W + c.tj] : 0ull;
+    }
+    typename G::Acc acc;
+    G::zero(acc);
+    G::run(reinterpret_cast<const uint16_t*>(X), poff, reinterpret_cast<const uint16_t*>(X), qoff, 2 * d,
+           c.n - c.ti * kTileF32, c.n - c.tj * kTileF32, lds, acc);   // its barriers publish inv and rbw
+    const int bl = brow + l31, b = c.tj * kTileF32 + bl;
+    const float ib = inv[kTileF32 + bl];
+    uint32_t pr[16];
+    unsigned nu = 0, nd = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int al = arow + 8 * (v >> 2) + (v & 3) + 4 * hi, a = c.ti * kTileF32 + al;
+      const bool pair = a < c.n && b < c.n && a != b;
+      float wv = acc[0][0][v] * inv[al] * ib;
+      if constexpr (HIST) {
+        bool hb = false, lb = false;
+        if constexpr (HIN) {
+          hb = (rbw[al] >> bl) & 1ull;
+          lb = (rbw[kTileF32 + al] >> bl) & 1ull;
+        }
+        wv = hb ? 1.0f : (lb ? 0.0f : wv);
+        if (pair && a < b) {
+          if (hb || lb) ++nd;
+          else ++nu;
         }
       }
-      rbw[0][rl] = h1;
-      rbw[1][rl] = l1;
+      pr[v] = pair && wv >= hp.h ? 1u : 0u;
+      if constexpr (HOUT) pr[v] |= (pair && wv > hp.S1 ? 2u : 0u) | (pair && wv < hp.S2 ? 4u : 0u);
     }
-    constexpr int PER = kTileF32 * KC / 256;
-    const int kk = tid % KC, r0 = tid / KC;
-    const float* pp[PER];
-    const float* qp[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int r = r0 + (256 / KC) * i;
-      pp[i] = X + static_cast<size_t>(pt[min(c.ti * kTileF32 + r, c.n - 1)]) * d + kk;
-      qp[i] = X + static_cast<size_t>(pt[min(c.tj * kTileF32 + r, c.n - 1)]) * d + kk;
+    if constexpr (HIST) {
+      if (nu) atomicAdd(&hp.stats[0], static_cast<unsigned long long>(nu));
+      if (nd) atomicAdd(&hp.stats[1], static_cast<unsigned long long>(nd));
+      if (tid == 0) atomicAdd(&hp.stats[2], 1ull);
     }
-    float vp[PER], vq[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      vp[i] = pp[i][0];
-      vq[i] = qp[i][0];
-    }
-    float acc[MT][MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < MT; ++j) acc[i][j] = 0.f;
-    for (int k0 = 0; k0 < d; k0 += KC) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        Ps[r0 + (256 / KC) * i][kk] = vp[i];
-        Qs[r0 + (256 / KC) * i][kk] = vq[i];
-      }
-      __syncthreads();
-      if (k0 + KC < d) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          vp[i] = pp[i][k0 + KC];
-          vq[i] = qp[i][k0 + KC];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < KC; ++k) {
-        float pa[MT], qb[MT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i) pa[i] = Ps[rb + i][k];
-#pragma unroll
-        for (int j = 0; j < MT; ++j) qb[j] = Qs[cb + j][k];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-          for (int j = 0; j < MT; ++j) acc[i][j] = fmaf(pa[i], qb[j], acc[i][j]);
-      }
-    }
-    unsigned long long nu = 0, nd = 0;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < MT; ++j) {
-        const int a = c.ti * kTileF32 + rb + i, b = c.tj * kTileF32 + cb + j;
-        const bool pair = a < c.n && b < c.n && a != b;
-        const bool hb = (rbw[0][rb + i] >> (cb + j)) & 1ull, lb = (rbw[1][rb + i] >> (cb + j)) & 1ull;
-        const float cs = acc[i][j] * inv_a[rb + i] * inv_b[cb + j];
-        const float wv = hb ? 1.0f : (lb ? 0.0f : cs);
-        uint8_t p = 0;
-        if (pair) {
-          p |= wv >= hp.h ? 1 : 0;
-          p |= wv > hp.S1 ? 2 : 0;
-          p |= wv < hp.S2 ? 4 : 0;
-          if (a < b) {
-            if (hb || lb) ++nd;
-            else ++nu;
-          }
-        }
-        pred[rb + i][cb + j] = p;
-      }
-    if (nu) atomicAdd(&hp.stats[0], nu);
-    if (nd) atomicAdd(&hp.stats[1], nd);
-    if (tid == 0) atomicAdd(&hp.stats[2], 1ull);
-    __syncthreads();
-    for (int idx = tid; idx < NM * kTileF32 * kGroupsF32; idx += 256) {
-      const int m = idx / (kTileF32 * kGroupsF32), rem = idx % (kTileF32 * kGroupsF32);
-      const int r = rem / kGroupsF32, g = rem % kGroupsF32;
-      uint32_t dv = 0, tv = 0;
-      for (int bit = 0; bit < 16; ++bit) {
-        dv |= static_cast<uint32_t>((pred[r][16 * g + bit] >> m) & 1) << bit;
-        tv |= static_cast<uint32_t>((pred[16 * g + bit][r] >> m) & 1) << bit;
-      }
-      dbits[m][r][g] = static_cast<uint16_t>(dv);
-      tbits[m][r][g] = static_cast<uint16_t>(tv);
-    }
+    block_bits<NM>(pr, reinterpret_cast<uint32_t*>(dw), reinterpret_cast<uint32_t*>(tw), arow, brow);
     __syncthreads();
     if (tid < 2 * kTileF32) {
       const bool mirror = tid >= kTileF32;
       const int rl = mirror ? tid - kTileF32 : tid;
-      int cnt = 0;
-      for (int g = 0; g < kGroupsF32; ++g) cnt += __popc(mirror ? tbits[0][rl][g] : dbits[0][rl][g]);
+      const int cnt = __popcll(mirror ? tw[rl] : dw[rl]);
       const int r = (mirror ? c.tj : c.ti) * kTileF32 + rl;
       if (cnt && r < c.n && (!mirror || c.ti != c.tj)) atomicAdd(&deg[c.lo + r], cnt);
     }
-    write_tile_words(c, dbits[0], tbits[0], bitmask, bmo);
+    write_tile_words(c, dw, tw, bitmask, bmo);
     if constexpr (HOUT) {
-      write_tile_words(c, dbits[1], tbits[1], hp.out_hi, bmo);
-      write_tile_words(c, dbits[2], tbits[2], hp.out_lo, bmo);
+      write_tile_words(c, dw + kTileF32, tw + kTileF32, hp.out_hi, bmo);
+      write_tile_words(c, dw + 2 * kTileF32, tw + 2 * kTileF32, hp.out_lo, bmo);
     }
     __syncthreads();
   }
@@ -2047,9 +1912,13 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
       launch("gram", gram_kernel_bf16<kGramPlain>, persistent_grid(), GramGemm::THREADS, 0, s, xb, d, perm_token,
              offsets, E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg, nullptr,
              nullptr, nullptr, T);
-    else
-      launch("gram", gram_kernel_f32, 2 * persistent_grid(), 256, 0, s, static_cast<const float*>(x), d, perm_token,
-             offsets, E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg);
+    else {
+      HistParams hp{};
+      hp.h = threshold;
+      launch("gram", gram_kernel_f32<false, false, false>, kGramF32Blocks * persistent_grid(), GemmF32::THREADS, 0, s,
+             static_cast<const float*>(x), d, perm_token, offsets, E, inv_norm_use, hp, ws.tile_off, ws.bm_off, ws.err,
+             ws.bitmask, ws.deg);
+    }
   } else {
     Carver cin(const_cast<void*>(hc->in)), cout(hc->out);
     const HistRec rin = carve_hist(cin, T, E, k, max_bucket);
@@ -2094,11 +1963,11 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
       else launch("gram", gram_hist_kernel_bf16<false, false>, g, th, 0, s, xb, LUFFY_GH_ARGS);
     } else {
       const float* xf = static_cast<const float*>(x);
-      const int g = 2 * persistent_grid();
-      if (hin && hout) launch("gram", gram_hist_kernel_f32<true, true>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
-      else if (hin) launch("gram", gram_hist_kernel_f32<true, false>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
-      else if (hout) launch("gram", gram_hist_kernel_f32<false, true>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
-      else launch("gram", gram_hist_kernel_f32<false, false>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
+      const int g = kGramF32Blocks * persistent_grid();
+      if (hin && hout) launch("gram", gram_kernel_f32<true, true, true>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
+      else if (hin) launch("gram", gram_kernel_f32<true, true, false>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
+      else if (hout) launch("gram", gram_kernel_f32<true, false, true>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
+      else launch("gram", gram_kernel_f32<true, false, false>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
     }
 #undef LUFFY_GH_ARGS
   }

@@ -1,17 +1,15 @@
 // luffy_expert_ffn: grouped FFN over the representatives of every expert,
 //   H = act(X_rep W1_e^T)   (rounded to the element type)
 //   Y = H W2_e^T
-// Row counts per expert live on the device: the bf16 kernels are persistent
-// (one block per CU) and find their tiles from rep_offsets; the fp32 grid
-// is sized from the upper bound ceil(max_rows/64) + E row tiles and blocks
-// without a tile exit.
+// Row counts per expert live on the device: the kernels are persistent (bf16:
+// one block per CU, float32: three) and find their tiles from rep_offsets.
 //
 // bf16: MFMA tiles of 256 weight rows by 256 or 320 token rows.  The weight
 // rows are the P operand and the token rows the Q operand, so each lane
 // ends with groups of four consecutive output columns of one row and stores
 // each as one 8-byte word.  The last row tile of an expert usually holds
 // fewer rows; its waves skip the MFMAs of the missing rows.
-// fp32: 64 x 64 tiles of plain FMA (4 x 4 per thread).
+// float32: 64 x 64 or 32 x 32 tiles of float32 MFMA.
 #include <type_traits>
 
 #include "gemm_core.h"
@@ -98,35 +96,6 @@ __device__ __forceinline__ float act_grad(float z) {
 // Epilogue codes of the backward's dA product: multiply by act'(Z) read
 // from a second buffer (dZ = dA * act'(Z)).
 constexpr int kActDzGelu = 3, kActDzSilu = 4;
-
-// Row tile q of the ragged row list: expert e, first row row0 and row count.
-// Wave-uniform; lane e handles expert e.  Returns false past the last tile.
-__device__ __forceinline__ bool locate_row_tile(const int32_t* __restrict__ rep_offsets, int E,
-                                                int BM, int q, int& e_out, int& row0, int& rows) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = 0, cnt = 0;
-  if (lane < E) {
-    lo = rep_offsets[lane];
-    hi = rep_offsets[lane + 1];
-    cnt = (hi - lo + BM - 1) / BM;
-  }
-  int incl = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
-  }
-  const uint64_t before = __ballot(lane < E && incl <= q);
-  const int e = __popcll(before);
-  if (e >= E) return false;
-  const int excl = __shfl(incl - cnt, e, 64);
-  const int elo = __shfl(lo, e, 64);
-  const int ehi = __shfl(hi, e, 64);
-  e_out = e;
-  row0 = elo + (q - excl) * BM;
-  rows = min(BM, ehi - row0);
-  return true;
-}
 
 // Tile shapes of the bf16 products: 256 output columns (weight rows, the P
 // operand) by up to 256 token rows (FfnGemm), or by up to 320 token rows
@@ -558,83 +527,160 @@ __global__ __launch_bounds__(256) void ffn_split_reduce_kernel(const int32_t* __
   }
 }
 
-constexpr int kF32Tile = 64;
+// float32 products.  Two tile shapes, chosen on the device from the actual
+// row counts (uniform over the grid):
+//  * 64 weight rows x 64 token rows on GemmF32 (float32 MFMA, LDS ring shared
+//    by four waves) when those tiles give every CU at least two;
+//  * else 32 x 32 tiles whose four waves each take a quarter of K, loaded
+//    straight into registers in fragment layout (nothing is shared between
+//    the waves, so no LDS staging and no barrier in the K loop), and add
+//    their partial tiles through LDS in wave order.  A small product is bound
+//    by the latency of its K loop, which this divides by four, and the finer
+//    tiles fill CUs that 64 x 64 tiles would leave idle.
+// On 8 experts of about 172 rows (512 -> 2048 -> 512) 64 x 64 tiles of vector
+// FMA took 98 and 188 us a product, these take 51 (64 x 64) and 70 us
+// (32 x 32); on 4 experts of 16 rows (256 -> 1024 -> 256) 21 and 64 us, now
+// 11 and 11 us.
+constexpr int kF32Blocks = 3;   // blocks a CU (48 KB of LDS each)
 
-// float32 products: 64 x 64 tiles, 4 x 4 outputs per thread, K in chunks of
-// 32 through LDS.  Each thread stages 8 elements of each operand per chunk;
-// its rows are fixed for the tile (looked up once), and the next chunk's
-// elements are loaded into registers while the current one is multiplied.
+struct F32Tiles {
+  int elo, ehi, mt, incl, NT, tiles, BT;
+  __device__ __forceinline__ F32Tiles(const int32_t* __restrict__ rep_offsets, int E, int N, int cus) {
+    const int lane = threadIdx.x & 63;
+    elo = lane < E ? rep_offsets[lane] : 0;
+    ehi = lane < E ? rep_offsets[lane + 1] : 0;
+    layout(64, N);
+    if (tiles < 2 * cus) layout(32, N);
+  }
+  // Tile t -> expert e, first token row, row count, first output column.
+  __device__ __forceinline__ void decode(int t, int E, int& e, int& row0, int& rows, int& n0) const {
+    const int lane = threadIdx.x & 63;
+    e = __popcll(__ballot(lane < E && incl <= t));
+    const int me = __shfl(mt, e, 64);
+    const int r = t - (__shfl(incl, e, 64) - me * NT);
+    row0 = __builtin_amdgcn_readfirstlane(__shfl(elo, e, 64) + r % me * BT);
+    rows = __builtin_amdgcn_readfirstlane(min(BT, __shfl(ehi, e, 64) - row0));
+    n0 = __builtin_amdgcn_readfirstlane(r / me * BT);
+  }
+
+ private:
+  // Tiles of bt x bt, expert by expert, the row tiles of one weight tile
+  // side by side.
+  __device__ __forceinline__ void layout(int bt, int N) {
+    const int lane = threadIdx.x & 63;
+    BT = bt;
+    NT = (N + bt - 1) / bt;
+    mt = (ehi - elo + bt - 1) / bt;
+    incl = mt * NT;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    tiles = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+  }
+};
+
+// Stores the 32 x 32 block of accumulators (lane l: token row l % 32, value v:
+// column 8 (v / 4) + v % 4 + 4 (l / 32)) to rows row0.. and columns n0..
 template <int ACT, bool FIRST>
-__global__ __launch_bounds__(256) void ffn_kernel_f32(
+__device__ __forceinline__ void store_block_f32(const f32x16& acc, int row0, int rows, int n0, int N,
+                                                float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, r = lane & 31;
+  if (r >= rows || n0 >= N) return;   // N is a multiple of 64, n0 of 32
+  float* dst = out + static_cast<size_t>(row0 + r) * N + n0 + 4 * (lane >> 5);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    float z[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      z[q] = acc[4 * g + q];
+      if constexpr (FIRST) z[q] = act_fn<ACT>(z[q]);
+    }
+    *reinterpret_cast<float4*>(dst + 8 * g) = make_float4(z[0], z[1], z[2], z[3]);
+  }
+}
+
+template <int ACT, bool FIRST>
+__global__ __launch_bounds__(GemmF32::THREADS, kF32Blocks) void ffn_kernel_f32(
     const float* __restrict__ A, const int32_t* __restrict__ row_index,
     const int32_t* __restrict__ rep_offsets, int E, int K, int N,
     const float* __restrict__ W, float* __restrict__ out) {
-  constexpr int KC = 32;
-  constexpr int PER = kF32Tile * KC / 256;   // staged elements per thread and operand
-  __shared__ float As[kF32Tile][KC + 1];
-  __shared__ float Bs[kF32Tile][KC + 1];
-  int e, row0, rows;
-  if (!locate_row_tile(rep_offsets, E, kF32Tile, blockIdx.x, e, row0, rows)) return;
-  const int tid = threadIdx.x;
-  const int n0 = blockIdx.y * kF32Tile;
-  const float* We = W + static_cast<size_t>(e) * N * K;
-  const int rb = (tid >> 4) * 4, cb = (tid & 15) * 4;
-  // staged element i of this thread: row r0 + 8i (r0 = tid / 32), column kk
-  const int kk = tid % KC, r0 = tid / KC;
-  const float* ap[PER];
-  const float* bp[PER];
+  using G = GemmF32;
+  static_assert(G::FM == 1 && G::FN == 1 && G::NWAVES == 4, "one 32 x 32 block a wave");
+  static_assert(G::LDS_BYTES >= 4 * 16 * 64 * 4, "partial tiles of the small shape");
+  __shared__ __attribute__((aligned(16))) uint8_t lds[G::LDS_BYTES];
+  const F32Tiles map(rep_offsets, E, N, gridDim.x / kF32Blocks);
+  const int lane = threadIdx.x & 63, w = G::wave();
+  for (int t = xcd_virtual_block(); t < map.tiles; t += gridDim.x) {
+    int e, row0, rows, n0;
+    map.decode(t, E, e, row0, rows, n0);
+    const float* We = W + static_cast<size_t>(e) * N * K;
+    if (map.BT == 64) {
+      uint32_t poff[G::LP], qoff[G::LQ];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int r = r0 + 8 * i;
-    const int m = row0 + min(r, rows - 1);
-    ap[i] = A + static_cast<size_t>(row_index ? row_index[m] : m) * K + kk;
-    bp[i] = We + static_cast<size_t>(min(n0 + r, N - 1)) * K + kk;
-  }
-  float va[PER], vb[PER];
+      for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(n0 + G::load_row(j)) * 2u * K;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    va[i] = ap[i][0];
-    vb[i] = bp[i][0];
-  }
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += KC) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      As[r0 + 8 * i][kk] = va[i];
-      Bs[r0 + 8 * i][kk] = vb[i];
+      for (int j = 0; j < G::LQ; ++j) {
+        const int m = row0 + min(G::load_row(G::LP + j) - G::BM, rows - 1);
+        qoff[j] = static_cast<uint32_t>(row_index ? row_index[m] : m) * 2u * K;
+      }
+      G::Acc acc;
+      G::zero(acc);
+      G::run(reinterpret_cast<const uint16_t*>(We), poff, reinterpret_cast<const uint16_t*>(A), qoff, 2 * K, 64, rows,
+             lds, acc);
+      const int qr = G::q_row(G::wave_n(w), 0);
+      store_block_f32<ACT, FIRST>(acc[0][0], row0 + qr, rows - qr, n0 + G::wave_m(w) * 32, N, out);
+      continue;
     }
-    __syncthreads();
-    if (k0 + KC < K) {
+    // lane l: weight row n0 + l % 32, token row l % 32, K values 8 s + 4 (l / 32) .. + 3 of step s
+    const int m = row0 + min(lane & 31, rows - 1);
+    const float* pw = We + static_cast<size_t>(n0 + (lane & 31)) * K + 4 * (lane >> 5);
+    const float* pa = A + static_cast<size_t>(row_index ? row_index[m] : m) * K + 4 * (lane >> 5);
+    const int nk = K / 32;                                   // 32-value chunks
+    const int c0 = w * nk / 4, c1 = (w + 1) * nk / 4;        // this wave's
+    constexpr int D = 3;                                     // chunks in flight
+    f32x4 fw[D][4], fa[D][4];
+    auto load = [&](int c, f32x4 (&w4)[4], f32x4 (&a4)[4]) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        va[i] = ap[i][k0 + KC];
-        vb[i] = bp[i][k0 + KC];
+      for (int u = 0; u < 4; ++u) {
+        w4[u] = *reinterpret_cast<const f32x4*>(pw + 32 * c + 8 * u);
+        a4[u] = *reinterpret_cast<const f32x4*>(pa + 32 * c + 8 * u);
+      }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int s = 0; s < D; ++s)
+      if (c0 + s < c1) load(c0 + s, fw[s], fa[s]);
+    // unrolled by D so that the register sets are indexed statically
+    for (int c = c0; c < c1; c += D) {
+#pragma unroll
+      for (int s = 0; s < D; ++s) {
+        if (c + s >= c1) break;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = mfma32x32x8_f32(fw[s][u], fa[s][u], acc);
+        if (c + s + D < c1) load(c + s + D, fw[s], fa[s]);
       }
     }
+    // partial tiles: value v of lane l of wave w at [w][v][l]; wave w then adds
+    // values 4w..4w+3 (columns 8w + 4 (l / 32) ..) of the four waves in order
+    float* part = reinterpret_cast<float*>(lds);
+    __syncthreads();   // the previous tile's sums are read
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-      float a[4], b[4];
+    for (int v = 0; v < 16; ++v) part[(w * 16 + v) * 64 + lane] = acc[v];
+    __syncthreads();
+    if ((lane & 31) < rows) {
+      float z[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[rb + i][c];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[cb + j][c];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (rb + i >= rows) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + cb + j;
-      if (n >= N) continue;
-      float z = acc[i][j];
-      if constexpr (FIRST) z = act_fn<ACT>(z);
-      out[static_cast<size_t>(row0 + rb + i) * N + n] = z;
+      for (int q = 0; q < 4; ++q) {
+        const float* p = part + (4 * w + q) * 64 + lane;
+        z[q] = ((p[0] + p[16 * 64]) + p[32 * 64]) + p[48 * 64];
+        if constexpr (FIRST) z[q] = act_fn<ACT>(z[q]);
+      }
+      *reinterpret_cast<float4*>(out + static_cast<size_t>(row0 + (lane & 31)) * N + n0 + 8 * w + 4 * (lane >> 5)) =
+          make_float4(z[0], z[1], z[2], z[3]);
     }
   }
 }
@@ -682,16 +728,11 @@ void launch_ffn(const void* x, const int32_t* row_index, const int32_t* rep_offs
              static_cast<uint16_t*>(y_rep), grid);
     }
   } else {
-    const int mt = (max_rows + kF32Tile - 1) / kF32Tile + E;
-    dim3 g1(mt, (d_ff + kF32Tile - 1) / kF32Tile), g2(mt, (d + kF32Tile - 1) / kF32Tile);
-    {
-      launch("ffn1", ffn_kernel_f32<ACT, true>, g1, 256, 0, s, static_cast<const float*>(x), row_index, rep_offsets,
-             E, d, d_ff, static_cast<const float*>(w1), static_cast<float*>(hidden));
-    }
-    {
-      launch("ffn2", ffn_kernel_f32<ACT, false>, g2, 256, 0, s, static_cast<const float*>(hidden), nullptr,
-             rep_offsets, E, d_ff, d, static_cast<const float*>(w2), static_cast<float*>(y_rep));
-    }
+    const int grid = kF32Blocks * persistent_grid();
+    launch("ffn1", ffn_kernel_f32<ACT, true>, grid, GemmF32::THREADS, 0, s, static_cast<const float*>(x), row_index,
+           rep_offsets, E, d, d_ff, static_cast<const float*>(w1), static_cast<float*>(hidden));
+    launch("ffn2", ffn_kernel_f32<ACT, false>, grid, GemmF32::THREADS, 0, s, static_cast<const float*>(hidden), nullptr,
+           rep_offsets, E, d_ff, d, static_cast<const float*>(w2), static_cast<float*>(y_rep));
   }
 }
 

@@ -33,6 +33,16 @@ __device__ __forceinline__ f32x16 mfma32x32x64_f8(i32x8 a, i32x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 127, 0, 127);
 }
 
+// One operand pair of the float32 product: 4 consecutive K values a lane,
+// multiplied by four v_mfma_f32_32x32x2_f32 (K value c of lanes 0-31 and of
+// lanes 32-63 together make product c; the sum over K takes its terms in any
+// order, so which K values a product pairs is free).
+__device__ __forceinline__ f32x16 mfma32x32x8_f32(f32x4 a, f32x4 b, f32x16 c) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], c, 0, 0, 0);
+  return c;
+}
+
 // Workgroup barrier without the memory fences of __syncthreads(): the fence
 // would make the compiler wait for every outstanding DMA load.  LDS
 // visibility is handled explicitly: each wave waits (vmcnt) for its own DMA
@@ -90,8 +100,13 @@ __device__ __forceinline__ int opaque_tid() {
 // two steps of v_mfma_scale_f32_32x32x64_f8f6f4, whose fragments are two
 // 16-byte chunks of a row (lanes 0-31 chunks 4s and 4s+1 of step s, lanes
 // 32-63 chunks 4s+2 and 4s+3).  The accumulator layout is the same.
+//
+// F32: the operands are float32 rows, also handed over as rows of 16-bit
+// units (two units a value), so a 64-unit stage holds 32 values of K in the
+// same eight 16-byte chunks a row; a fragment is one chunk (4 values) and a
+// step four v_mfma_f32_32x32x2_f32.  The accumulator layout is the same.
 template <int BM_, int BN_, int WM_, int WN_, bool MFAST_, bool QIL_, int BK_ = 64, int STAGES_ = 2,
-          bool PT_ = false, bool QT_ = false, bool F8_ = false>
+          bool PT_ = false, bool QT_ = false, bool F8_ = false, bool F32_ = false>
 struct GemmCore {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr bool QIL = QIL_;
@@ -114,6 +129,8 @@ struct GemmCore {
   static constexpr int RPI = 64 / CPR;               // rows per DMA instruction
   static constexpr bool F8 = F8_;
   static_assert(!F8 || (BK == 64 && !PT && !QT), "fp8 operands: row-major, 64-unit stages");
+  static constexpr bool F32 = F32_;
+  static_assert(!F32 || (!F8 && !PT && !QT), "float32 operands: row-major");
   static constexpr int STEPS = F8 ? BK / 32 : BK / 16;   // MFMA K steps per stage
   static constexpr int READS = F8 ? 2 : 1;               // LDS reads per fragment
   static constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
@@ -246,7 +263,8 @@ struct GemmCore {
 
   // Fragments of one 16-wide K step (chunks 2*step and 2*step+1 of every
   // row: lanes 0-31 take the low chunk, lanes 32-63 the high one).
-  using Frag = std::conditional_t<F8, i32x8, bf16x8>;
+  using Frag = std::conditional_t<F8, i32x8, std::conditional_t<F32, f32x4, bf16x8>>;
+  static constexpr int MPF = F32 ? 4 : 1;   // MFMA instructions per fragment pair
   struct Frags {
     Frag a[FM], b[FN];
   };
@@ -303,8 +321,8 @@ struct GemmCore {
       } else {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
-          f.a[i] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(S + prow0 +
-                                                                                        32 * i * ROW_BYTES + pc);
+          f.a[i] = *reinterpret_cast<const __attribute__((address_space(3))) Frag*>(S + prow0 + 32 * i * ROW_BYTES +
+                                                                                      pc);
       }
       if constexpr (QT) {
         const int wn = wave_n(wave());
@@ -313,8 +331,8 @@ struct GemmCore {
       } else {
 #pragma unroll
         for (int j = 0; j < NQ; ++j)
-          f.b[j] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(S + qrow0 +
-                                                                                        QSTEP * j * ROW_BYTES + pc);
+          f.b[j] = *reinterpret_cast<const __attribute__((address_space(3))) Frag*>(S + qrow0 + QSTEP * j * ROW_BYTES +
+                                                                                      pc);
       }
     }
   }
@@ -326,6 +344,7 @@ struct GemmCore {
 #pragma unroll
       for (int j = 0; j < NQ; ++j) {
         if constexpr (F8) acc[i][j] = mfma32x32x64_f8(f.a[i], f.b[j], acc[i][j]);
+        else if constexpr (F32) acc[i][j] = mfma32x32x8_f32(f.a[i], f.b[j], acc[i][j]);
         else acc[i][j] = mfma32x32x16(f.a[i], f.b[j], acc[i][j]);
       }
   }
@@ -335,7 +354,7 @@ struct GemmCore {
   // next step starts.
   template <int NQ>
   static __device__ __forceinline__ void interleave_reads() {
-    constexpr int NMF = FM * NQ, NDS = NQ > 0 ? READS * (FM + NQ) : 0;
+    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS * (FM + NQ) : 0;
 #pragma unroll
     for (int i = 0; i < NMF; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
@@ -350,7 +369,7 @@ struct GemmCore {
   // latency is the longer one.
   template <int NQ>
   static __device__ __forceinline__ void interleave_loads() {
-    constexpr int NMF = FM * NQ, NDS = NQ > 0 ? READS * (FM + NQ) : 0, NVM = LOADS;
+    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS * (FM + NQ) : 0, NVM = LOADS;
     constexpr int PV = NMF < NVM ? NMF : NVM;
     constexpr int PD = (NMF - PV) < NDS ? (NMF - PV) : NDS;
 #pragma unroll
@@ -623,6 +642,10 @@ struct GemmCore {
 using GemmBig64 = GemmCore<256, 256, 2, 4, false, false>;
 // The same on fp8 rows: 128 values of K a stage.
 using GemmBig64F8 = GemmCore<256, 256, 2, 4, false, false, 64, 2, false, false, true>;
+// float32 rows: 64 x 64, 256 threads, wave tile 32 x 32, three 32-value
+// stages (48 KB: three blocks a CU, whose loads, products and epilogues
+// overlap).
+using GemmF32 = GemmCore<64, 64, 2, 2, false, false, 64, 3, false, false, false, true>;
 // 256 x 256, 512 threads, wave tile 64 x 128 (SIMD s holds P rows
 // 64s..64s+63 of both Q halves), 64-wide stages.
 using GemmRagged64 = GemmCore<256, 256, 4, 2, true, false>;

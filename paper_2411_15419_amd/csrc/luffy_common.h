@@ -14,9 +14,10 @@ namespace luffy {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-union Pack16 {          // 16 bytes seen as 8 bf16 or raw words
+union Pack16 {          // 16 bytes seen as 8 bf16, 4 float32 or raw words
   uint4 u4;
   uint16_t h[8];
+  float f[4];
   bf16x8 v;
 };
 

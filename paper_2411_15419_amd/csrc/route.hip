@@ -3,7 +3,7 @@
 // Kernels (all on the caller's stream, no host synchronisation):
 //   gate_kernel      32 or 64 tokens per block; the four waves split the
 //                    contraction over d and accumulate tokens x E logit tiles
-//                    on MFMA (16x16x32); fp32: plain FMA.  The epilogue
+//                    on MFMA (16x16x32; float32 16x16x4).  The epilogue
 //                    takes top-k, gates and the float64 re-decision of close
 //                    calls, then ranks every slot among the block's slots of
 //                    the same expert (wave ballots) and writes the block's
@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "luffy_common.h"
 
@@ -32,10 +33,10 @@ namespace {
 
 // Tokens per gate block (= slots per chunk of the histogram): 64, or 32
 // when 64 would leave most CUs without a block (T below 32768 makes fewer
-// than 512 blocks of 64).  Depends on T only, so workspace sizing and the
-// launches always agree.
+// than 512 blocks of 64), or 16 when 32 would leave CUs without one.
+// Depends on T only, so workspace sizing and the launches always agree.
 constexpr int kGateTokMax = 64;
-inline int gate_tokens(int T) { return T >= 32768 ? 64 : 32; }
+inline int gate_tokens(int T) { return T >= 32768 ? 64 : (T >= 8192 ? 32 : 16); }
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
   // xor butterfly: every lane ends with the same, bit-identical sum
@@ -258,11 +259,14 @@ __device__ __forceinline__ void gate_select(const float* lg, const float* bias, 
   }
 }
 
-// One block of four waves per chunk of 64 tokens.  bf16: wave w takes the
+// One block of four waves per chunk of TOK tokens.  bf16: wave w takes the
 // w-th quarter of the contraction over d and accumulates the 64 x E logits
-// of the chunk on MFMA (16x16x32: four 16-token blocks per 16-expert
+// of the chunk on MFMA (16x16x32: TOK/16 16-token blocks per 16-expert
 // block), two K steps' token and weight loads in flight at a time; the four
-// partial tiles are added in LDS in a fixed order.  fp32: plain FMA.  Wave 0 then
+// partial tiles are added in LDS in a fixed order.  float32: the same on
+// 16x16x4 float32 MFMA, 16 values of d a K step (3001 tokens of d = 512, 8
+// experts: 92 us with one token a lane and plain FMA, whose loads do not
+// coalesce, 10 us so).  Wave 0 then
 // runs the epilogue for the chunk (lane = token): top-k, gates, the float64
 // re-decision of close calls, and the rank of every slot among the chunk's
 // slots of the same expert (wave ballots) with the chunk's per-expert
@@ -294,24 +298,38 @@ __global__ __launch_bounds__(256) void gate_kernel(
   if (threadIdx.x < E) bias[threadIdx.x] = bias_g ? bias_g[threadIdx.x] : 0.f;
   if (blockIdx.x == 0 && threadIdx.x == 0) *scan_done = 0;   // armed for slot_scan_kernel
 
-  if constexpr (BF16) {
-    const uint16_t* X = static_cast<const uint16_t*>(xv);
-    const uint16_t* W = static_cast<const uint16_t*>(wv);
+  {
+    // a K step is 16 bytes a lane: KS values of every row, VL of them in each
+    // of the four lane groups
+    using Elem = std::conditional_t<BF16, uint16_t, float>;
+    constexpr int VL = 16 / sizeof(Elem), KS = 4 * VL;
+    const Elem* X = static_cast<const Elem*>(xv);
+    const Elem* W = static_cast<const Elem*>(wv);
+    auto mma = [](const Pack16& p, const Pack16& q, f32x4 c) {
+      if constexpr (BF16) {
+        return mfma16x16x32(p.v, q.v, c);
+      } else {
+        // value u of the four lane groups together is one 16x16x4 product
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_16x16x4f32(p.f[u], q.f[u], c, 0, 0, 0);
+        return c;
+      }
+    };
     const int nE16 = (E + 15) >> 4;
     f32x4 acc[kGateA][4];
 #pragma unroll
     for (int i = 0; i < kGateA; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint16_t* arow[kGateA];
+    const Elem* arow[kGateA];
 #pragma unroll
     for (int i = 0; i < kGateA; ++i)
-      arow[i] = X + static_cast<size_t>(min(t0 + 16 * i + (lane & 15), T - 1)) * d + 8 * (lane >> 4);
-    const uint16_t* brow[4];
+      arow[i] = X + static_cast<size_t>(min(t0 + 16 * i + (lane & 15), T - 1)) * d + VL * (lane >> 4);
+    const Elem* brow[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      brow[j] = W + static_cast<size_t>(min(16 * j + (lane & 15), E - 1)) * d + 8 * (lane >> 4);
-    const int nsteps = d / 32;
+      brow[j] = W + static_cast<size_t>(min(16 * j + (lane & 15), E - 1)) * d + VL * (lane >> 4);
+    const int nsteps = d / KS;
     const int q = (nsteps + 3) / 4;
     const int s_lo = w * q, s_hi = min(nsteps, s_lo + q);
     constexpr int B = 2;   // K steps per batch; the next batch is loaded while one is multiplied
@@ -328,10 +346,10 @@ __global__ __launch_bounds__(256) void gate_kernel(
         const bool in = st < s_hi;
 #pragma unroll
         for (int i = 0; i < kGateA; ++i)
-          aa[u][i].u4 = in ? *reinterpret_cast<const uint4*>(arow[i] + 32 * st) : make_uint4(0, 0, 0, 0);
+          aa[u][i].u4 = in ? *reinterpret_cast<const uint4*>(arow[i] + KS * st) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          bb[u][j].u4 = (in && j < nE16) ? *reinterpret_cast<const uint4*>(brow[j] + 32 * st)
+          bb[u][j].u4 = (in && j < nE16) ? *reinterpret_cast<const uint4*>(brow[j] + KS * st)
                                          : make_uint4(0, 0, 0, 0);
       }
     };
@@ -342,12 +360,12 @@ __global__ __launch_bounds__(256) void gate_kernel(
         for (int j = 0; j < 4; ++j)
           if (j < nE16)
 #pragma unroll
-            for (int i = 0; i < kGateA; ++i) acc[i][j] = mfma16x16x32(aa[u][i].v, bb[u][j].v, acc[i][j]);
+            for (int i = 0; i < kGateA; ++i) acc[i][j] = mma(aa[u][i], bb[u][j], acc[i][j]);
       if (inv_norm) {
 #pragma unroll
         for (int u = 0; u < B; ++u)
 #pragma unroll
-          for (int i = 0; i < kGateA; ++i) accsq[i] = mfma16x16x32(aa[u][i].v, aa[u][i].v, accsq[i]);
+          for (int i = 0; i < kGateA; ++i) accsq[i] = mma(aa[u][i], aa[u][i], accsq[i]);
       }
     };
     if (s_lo < s_hi) load(s_lo, a[0], b[0]);
@@ -379,25 +397,6 @@ __global__ __launch_bounds__(256) void gate_kernel(
       for (int j = 0; j < 4; ++j)
         if (j < nE16)
           *reinterpret_cast<f32x4*>(&part[w][16 * j + (lane & 15)][16 * i + 4 * (lane >> 4)]) = acc[i][j];
-  } else {
-    // float32 inputs: lane = token (lanes past TOK have none), experts
-    // strided over the four waves
-    const float* X = static_cast<const float*>(xv);
-    const float* W = static_cast<const float*>(wv);
-    const int t = min(t0 + lane, T - 1);
-    for (int e = w; e < E && lane < TOK; e += 4) {
-      float s = 0.f;
-      for (int i = 0; i < d; ++i) s = fmaf(X[static_cast<size_t>(t) * d + i], W[static_cast<size_t>(e) * d + i], s);
-      part[0][e][lane] = s;
-      part[1][e][lane] = 0.f;
-      part[2][e][lane] = 0.f;
-      part[3][e][lane] = 0.f;
-    }
-    if (inv_norm && lane < TOK) {
-      float s = 0.f;
-      for (int i = w; i < d; i += 4) s = fmaf(X[static_cast<size_t>(t) * d + i], X[static_cast<size_t>(t) * d + i], s);
-      sumsq[w][lane] = s;
-    }
   }
   __syncthreads();
   if (inv_norm && threadIdx.x < TOK && t0 + static_cast<int>(threadIdx.x) < T) {
@@ -849,10 +848,12 @@ void route_enqueue(const void* x, int T, int d, int dtype, const void* w_gate, c
   } else {
 #define LUFFY_GATE_ARGS x, w_gate, b_gate, T, d, E, k, topk_idx, topk_gate, slot_pos, ws.hist, ws.done, inv_norm
     if (dtype == LUFFY_BF16) {
-      if (tok == 32) launch("gate", gate_kernel<true, 32>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
+      if (tok == 16) launch("gate", gate_kernel<true, 16>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
+      else if (tok == 32) launch("gate", gate_kernel<true, 32>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
       else launch("gate", gate_kernel<true, kGateTokMax>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
     } else {
-      if (tok == 32) launch("gate", gate_kernel<false, 32>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
+      if (tok == 16) launch("gate", gate_kernel<false, 16>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
+      else if (tok == 32) launch("gate", gate_kernel<false, 32>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
       else launch("gate", gate_kernel<false, kGateTokMax>, gblocks, 256, 0, s, LUFFY_GATE_ARGS);
     }
 #undef LUFFY_GATE_ARGS
