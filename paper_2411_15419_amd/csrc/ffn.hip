@@ -268,11 +268,12 @@ __device__ __forceinline__ void ffn_tile(const uint16_t* __restrict__ A, const i
   const int tid = opaque_tid(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = G::wave_m(w), wn = G::wave_n(w);
   uint32_t poff[G::LP], qoff[G::LQ];
+  // weights [N, K] row-major, or (G::PT) [K, N]: element (k, n) at k * N + n
+  if constexpr (G::PT) {
+    G::kmajor_offsets(poff, G::SLOTS_P, N, n0, N - n0);
+  } else {
 #pragma unroll
-  for (int j = 0; j < G::LP; ++j) {
-    // weights [N, K] row-major, or (G::PT) [K, N]: element (k, n) at k * N + n
-    if constexpr (G::PT) poff[j] = G::kmajor_offset(j, N, n0, N - n0);
-    else poff[j] = static_cast<uint32_t>(min(n0 + G::load_row(j), N - 1)) * K;
+    for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(min(n0 + G::load_row(j), N - 1)) * K;
   }
 #pragma unroll
   for (int j = 0; j < G::LQ; ++j) {
@@ -778,22 +779,22 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restr
   }
 }
 
-// First row and K extent (R_e rounded up to 64) of expert e.
-__device__ __forceinline__ void expert_rows(const int32_t* __restrict__ rep_offsets, int e, int& lo, int& re) {
-  lo = rep_offsets[e];
-  re = rep_offsets[e + 1] - lo;
-}
-
 // Weight gradients: out[e][i][j] = sum over the expert's rows r of
 // P[r][i] Q[r][j], P [*, M] and Q [*, N] row-major token rows (both read
 // K-major: the contraction runs over rows); float32 output [E][M][N]; an
 // expert without rows gets zeros.
 using WgradGemm = GemmCore<256, 256, 2, 4, false, false, 64, 2, true, true>;
 
-// OUT_BF16: the sums are rounded to bf16 (the weights' own type), stored
-// four bytes at a time: lanes l and l^1 hold neighbouring columns of the
-// same rows and swap one value, so that the even lane stores its row v and
-// the odd lane row v+1, two columns each.
+// OUT_BF16: the sums are rounded to bf16 (the weights' own type).
+// A tile has few K stages (an expert's rows / 64), so its fixed costs count:
+// the operand fragments' addresses are registers and immediates, not
+// recomputed per read (gemm_core.h), the stores carry no vector address
+// arithmetic and write whole lines, and the tile order lets an XCD share its
+// panels.  16 experts of about 250 rows, float32, 1024 x 4096 each: 112 -> 85
+// us a gradient; bf16, 2048 x 8192 each, 4095 rows in all: 465 -> 270 us.  Not
+// kept: 128 x 128 tiles at two blocks a CU (117 and 385 us; twice the LDS
+// traffic a product), the next tile's first stages issued before the stores
+// (slower by 1-7%: the loads wait behind the stores either way).
 template <bool OUT_BF16>
 __global__ __launch_bounds__(WgradGemm::THREADS) void wgrad_kernel(const uint16_t* __restrict__ P,
                                                                    const uint16_t* __restrict__ Q,
@@ -802,64 +803,67 @@ __global__ __launch_bounds__(WgradGemm::THREADS) void wgrad_kernel(const uint16_
   using G = WgradGemm;
   __shared__ __attribute__((aligned(16))) uint8_t lds[G::LDS_BYTES];
   const int mt = (M + G::BM - 1) / G::BM, nt = (N + G::BN - 1) / G::BN;
-  const int tpe = mt * nt;
-  for (int t = blockIdx.x; t < E * tpe; t += gridDim.x) {
-    const int e = t / tpe, r = t - e * tpe;
-    const int m0 = (r / nt) * G::BM, n0 = (r % nt) * G::BN;
-    int lo, re;
-    expert_rows(rep_offsets, e, lo, re);
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    re = __builtin_amdgcn_readfirstlane(re);
+  const int tpe = mt * nt, total = E * tpe;
+  // rows of expert e in lane e (E <= 64): a tile starts without a load
+  const int eln = threadIdx.x & 63;
+  const int elo = eln < E ? rep_offsets[eln] : 0, ehi = eln < E ? rep_offsets[eln + 1] : 0;
+  for (int t = xcd_virtual_block(); t < total; t += gridDim.x) {
+    // column tiles in groups of 4, row tiles next, columns fastest: the 32
+    // tiles that run together on an XCD share 8 row and 4 column panels
+    const int e = t / tpe, r = t - e * tpe, g = r / (4 * mt), r2 = r - g * 4 * mt, wd = min(4, nt - 4 * g);
+    const int m0 = r2 / wd * G::BM, n0 = (4 * g + r2 % wd) * G::BN;
+    const int lo = __builtin_amdgcn_readlane(elo, e), re = __builtin_amdgcn_readlane(ehi, e) - lo;
+    uint32_t poff[G::LP], qoff[G::LQ];
+    G::kmajor_offsets(poff, G::SLOTS_P, M, m0, M - m0);
+    G::kmajor_offsets(qoff, G::SLOTS_Q, N, n0, N - n0);
     typename G::Acc acc;
     G::zero(acc);
-    if (re > 0) {
-      uint32_t poff[G::LP], qoff[G::LQ];
+    // an expert without rows has no stage and its sums stay zero
+    G::template run<G::FN>(P + static_cast<size_t>(lo) * M, poff, Q + static_cast<size_t>(lo) * N, qoff,
+                           (re + 63) / 64 * 64, M - m0, N - n0, lds, acc, M, N, re);
+    __builtin_amdgcn_sched_barrier(0);
+    // The tile's corner is the base of a buffer resource, a lane's column (and
+    // its four-row half) its offset, and a row a scalar offset, so a store
+    // costs no vector arithmetic.  M and N are multiples of 64: a wave's 32-row
+    // and 64-column blocks are inside the matrix or outside as a whole, and
+    // those outside get a resource of no bytes, whose stores are dropped.
+    const int lane = opaque_tid() & 63, w = G::wave();
+    const int l31 = lane & 31, hi = lane >> 5;
+    const int r0 = G::wave_m(w) * G::WTM, c0 = G::q_row(G::wave_n(w), 0);
+    constexpr int ES = OUT_BF16 ? 2 : 4;
+    uint8_t* corner = static_cast<uint8_t*>(out) + ((static_cast<size_t>(e) * M + m0) * N + n0) * ES;
+    static_assert(G::FN == 2, "column blocks are stored in pairs");
 #pragma unroll
-      for (int j = 0; j < G::LP; ++j) poff[j] = G::kmajor_offset(j, M, m0, M - m0);
+    for (int fm = 0; fm < G::FM; ++fm) {
+      const bool in = n0 + c0 < N && m0 + r0 + 32 * fm < M;
+      const __amdgpu_buffer_rsrc_t ors = G::rsrc(corner, in ? G::kRange : 0u);
+      if constexpr (OUT_BF16) {
+        // a store is four bytes a lane, a whole 128-byte line (64 columns) of
+        // two rows: of lanes l and l^1, which hold neighbouring columns of both
+        // 32-column blocks, the even one stores the pair of the first block and
+        // the odd one that of the second
+        const bool odd = lane & 1;
+        const uint32_t voff = (static_cast<uint32_t>(4 * hi) * N + c0 + (odd ? 32 : 0) + (l31 & ~1)) * 2u;
 #pragma unroll
-      for (int j = 0; j < G::LQ; ++j) qoff[j] = G::kmajor_offset(G::LP + j, N, n0, N - n0);
-      G::template run<G::FN>(P + static_cast<size_t>(lo) * M, poff, Q + static_cast<size_t>(lo) * N, qoff,
-                             (re + 63) / 64 * 64, M - m0, N - n0, lds, acc, M, N, re);
-    }
-    const int tid = opaque_tid(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = G::wave_m(w), wn = G::wave_n(w);
-    if constexpr (OUT_BF16) {
-      uint16_t* oe = static_cast<uint16_t*>(out) + static_cast<size_t>(e) * M * N;
-      const bool odd = lane & 1;
-#pragma unroll
-      for (int fm = 0; fm < G::FM; ++fm)
-#pragma unroll
-        for (int fn = 0; fn < G::FN; ++fn) {
-          // first column of the lane pair; N is a multiple of 64, so both
-          // columns are in range or neither is (same for both lanes)
-          const int jp = (n0 + G::q_row(wn, fn) + (lane & 31)) & ~1;
-          if (jp >= N) continue;
-#pragma unroll
-          for (int v = 0; v < 16; v += 2) {
-            // the even lane needs the odd lane's row-v value, the odd lane
-            // the even lane's row-(v+1) value
-            const float recv = __shfl_xor(odd ? acc[fm][fn][v] : acc[fm][fn][v + 1], 1, 64);
-            const float lo = odd ? recv : acc[fm][fn][v];
-            const float hi = odd ? acc[fm][fn][v + 1] : recv;
-            const int i = m0 + wm * G::WTM + 32 * fm + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4) + (odd ? 1 : 0);
-            if (i < M)
-              *reinterpret_cast<uint32_t*>(oe + static_cast<size_t>(i) * N + jp) = pack_bf16x2(lo, hi);
-          }
+        for (int v = 0; v < 16; ++v) {
+          const float own = odd ? acc[fm][1][v] : acc[fm][0][v], snd = odd ? acc[fm][0][v] : acc[fm][1][v];
+          const float rcv = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+              0, static_cast<int>(__float_as_uint(snd)), 0xB1, 0xF, 0xF, false)));   // quad_perm [1, 0, 3, 2]: lane ^ 1
+          const uint32_t word = pack_bf16x2(odd ? rcv : own, odd ? own : rcv);
+          __builtin_amdgcn_raw_buffer_store_b32(word, ors, voff, (r0 + 32 * fm + 8 * (v / 4) + v % 4) * N * 2, 0);
         }
-    } else {
-      float* oe = static_cast<float*>(out) + static_cast<size_t>(e) * M * N;
+      } else {
+        const uint32_t voff = (static_cast<uint32_t>(4 * hi) * N + c0 + l31) * 4u;
 #pragma unroll
-      for (int fm = 0; fm < G::FM; ++fm)
-#pragma unroll
-        for (int fn = 0; fn < G::FN; ++fn) {
-          const int j = n0 + G::q_row(wn, fn) + (lane & 31);
-          if (j >= N) continue;
+        for (int fn = 0; fn < G::FN; ++fn)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            const int i = m0 + wm * G::WTM + 32 * fm + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-            if (i < M) oe[static_cast<size_t>(i) * N + j] = acc[fm][fn][v];
+            float f = acc[fm][fn][v];
+            asm volatile("" : "+v"(f));   // one register out of the tuple at a time
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(f), ors, voff + 128 * fn,
+                                                  (r0 + 32 * fm + 8 * (v / 4) + v % 4) * N * 4, 0);
           }
-        }
+      }
     }
   }
 }

@@ -132,7 +132,7 @@ struct GemmCore {
   static constexpr bool F32 = F32_;
   static_assert(!F32 || (!F8 && !PT && !QT), "float32 operands: row-major");
   static constexpr int STEPS = F8 ? BK / 32 : BK / 16;   // MFMA K steps per stage
-  static constexpr int READS = F8 ? 2 : 1;               // LDS reads per fragment
+  static constexpr int READS_P = F8 || PT ? 2 : 1, READS_Q = F8 || QT ? 2 : 1;   // LDS reads per fragment
   static constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
   static constexpr int NWAVES = WM * WN;
@@ -171,22 +171,30 @@ struct GemmCore {
     return (w + NWAVES * j) * RPI + lane / CPR;
   }
 
-  // K-major operand, load j (P: j < LP, Q: j >= LP): the k row (0..BK-1) this
-  // lane fills, and the element offset, at k = 0, of the 8 values it
-  // fetches: k_row * ld + m_first + 8 * (slot ^ swz_t(k_row)); 0xFFFFFFFF
-  // when those columns are at or past m_valid (not fetched).
-  static __device__ __forceinline__ int kmajor_row(int j) {
-    const int w = wave(), lane = opaque_tid() & 63;
-    const bool isp = j < LP;
-    const int slots = isp ? SLOTS_P : SLOTS_Q;
-    return (w + NWAVES * (isp ? j : j - LP)) * (64 / slots) + lane / slots;
+  // K-major operand (P: SLOTS_P, Q: SLOTS_Q slots): the k row (0..BK-1) this
+  // lane fills in the operand's first load of a stage (load j fills the row
+  // KSTEP * j further on, in the same columns, since KSTEP is a multiple of
+  // swz_t's period), and the element offset, at k = 0, of the 8 values it
+  // fetches there: k_row * ld + m_first + 8 * (slot ^ swz_t(k_row));
+  // 0xFFFFFFFF when those columns are at or past m_valid (not fetched).
+  static constexpr int KSTEP_P = NWAVES * (64 / SLOTS_P), KSTEP_Q = NWAVES * (64 / SLOTS_Q);
+  static_assert((!PT || KSTEP_P % 8 == 0) && (!QT || KSTEP_Q % 8 == 0), "K-major load rows");
+  static __device__ __forceinline__ int kmajor_row(int slots) {
+    return wave() * (64 / slots) + (opaque_tid() & 63) / slots;
   }
-  static __device__ __forceinline__ uint32_t kmajor_offset(int j, int ld, int m_first, int m_valid) {
+  static __device__ __forceinline__ uint32_t kmajor_offset(int slots, int ld, int m_first, int m_valid) {
     const int lane = opaque_tid() & 63;
-    const int slots = j < LP ? SLOTS_P : SLOTS_Q;
-    const int kr = kmajor_row(j);
+    const int kr = kmajor_row(slots);
     const int m = 8 * ((lane % slots) ^ swz_t(kr));
     return m < m_valid ? static_cast<uint32_t>(kr) * ld + m_first + m : 0xFFFFFFFFu;
+  }
+  // the offsets of run() / prefetch() for a K-major operand: only entry 0 is used
+  template <int N>
+  static __device__ __forceinline__ void kmajor_offsets(uint32_t (&off)[N], int slots, int ld, int m_first,
+                                                        int m_valid) {
+    off[0] = kmajor_offset(slots, ld, m_first, m_valid);
+#pragma unroll
+    for (int j = 1; j < N; ++j) off[j] = 0;
   }
 
   static __device__ __forceinline__ void zero(Acc& acc) {
@@ -208,20 +216,23 @@ struct GemmCore {
   // prove uniformity; a resource in vector registers would wrap every DMA
   // instruction in a readfirstlane loop.
   static constexpr uint32_t kRange = 0xFFFF0000u;
-  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base) {
+  static __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, uint32_t range = kRange) {
     const uint64_t v = reinterpret_cast<uint64_t>(base);
     const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v)));
     const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32)));
     return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((hi << 32) | lo), static_cast<short>(0),
-                                             static_cast<int>(kRange), 0x00020000);
+                                             static_cast<int>(range), 0x00020000);
   }
 
   // Stage kt: a row-major operand advances by the scalar offset kt*BK*2; a
-  // K-major one by kt*BK rows of ld elements in its per-lane offset, and its
-  // rows at or past kvalid are not fetched (they read as zeros).
+  // K-major one by kt*BK rows of ld elements in its per-lane offset (one add
+  // of a wave-uniform value), and its rows at or past kvalid are not fetched
+  // (they read as zeros).  krow[0], krow[1]: kmajor_row of P and Q, or
+  // kNoRow for a lane whose columns are not fetched.
+  static constexpr int kNoRow = 0x7fffffff;
   static __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t prs, __amdgpu_buffer_rsrc_t qrs,
                                                const uint32_t (&goff)[LOADS], int kt, lds_ptr st, int w,
-                                               int pld = 0, int qld = 0, int kvalid = 0x7fffffff) {
+                                               int pld, int qld, int kvalid, const int (&krow)[2]) {
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       lds_ptr dst = st + (w + NWAVES * j) * 1024;
@@ -230,8 +241,9 @@ struct GemmCore {
       int soff = kt * BK * 2;
       if (kmaj) {
         const int ld = j < LP ? pld : qld;
-        const bool ok = off != kRange && kt * BK + kmajor_row(j) < kvalid;
-        off = ok ? off + static_cast<uint32_t>(kt * BK) * static_cast<uint32_t>(ld) * 2u : kRange;
+        const int k0 = kt * BK + (j < LP ? KSTEP_P * j : KSTEP_Q * (j - LP));
+        off = goff[j < LP ? 0 : LP] + static_cast<uint32_t>(k0) * static_cast<uint32_t>(ld) * 2u;
+        off = krow[j < LP ? 0 : 1] < kvalid - k0 ? off : kRange;
         soff = 0;
       }
       __builtin_amdgcn_raw_ptr_buffer_load_lds(j < LP ? prs : qrs,
@@ -250,8 +262,7 @@ struct GemmCore {
     for (int j = 0; j < LOADS; ++j) {
       if (j < LP ? PT : QT) {
         // K-major: the caller's kmajor_offset already places the 8 values
-        const uint32_t o = j < LP ? poff[j] : qoff[j - LP];
-        goff[j] = o == 0xFFFFFFFFu ? kRange : o * 2u;
+        goff[j] = (j < LP ? poff[j] : qoff[j - LP]) * 2u;
         continue;
       }
       const int r = load_row(j);
@@ -277,34 +288,79 @@ struct GemmCore {
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   }
 
-  // K step `step` of the stage at S, first NQ Q blocks.
-  // One fragment of a K-major operand whose stage region starts at R (row
-  // pitch PITCH bytes): lane l (group g = l/16, c = l%16) gets m = m_blk +
-  // 16*(g%2) + c and k = 16*step + 8*(g/2) + 0..7, as the row-major read
-  // does.  In each 16-lane group the transposing read hands lane c the
-  // values (k0 + 0..3, m0 + c) when lane c addresses (k0 + c/4, m0 + 4*(c%4)).
+  // Fragments of a K-major operand (stage region of row pitch PITCH bytes,
+  // this wave's rows starting at m_wave, a multiple of 32): lane l (group
+  // g = l/16, c = l%16) gets m = m_wave + 32 i + 16*(g%2) + c and k = 16*step
+  // + 8*(g/2) + 0..7 of block i, as the row-major read does.  In each 16-lane
+  // group the transposing read hands lane c the values (k0 + 0..3, m0 + c)
+  // when lane c addresses (k0 + c/4, m0 + 4*(c%4)); two reads (u = 0, 1) make
+  // a fragment.  The address of read u of block i in step s is
+  //   16 s PITCH + 4 u PITCH + base ^ 64 (i & 1) ^ 128 ((i >> 1 & 1) ^ u) + 256 (i >> 2)
+  // with one per-lane base: 4 u changes swz_t by 8 slots, 32 i adds 4 i
+  // slots below the wave's 4 FM (FN) aligned ones.  The four bases the XORs
+  // give are kept in registers and the rest is an immediate, so a fragment
+  // costs no address arithmetic (recomputed per fragment it was 25 vector
+  // operations, three MFMAs' time).
   template <int PITCH>
-  static __device__ __forceinline__ bf16x8 read_kmajor(lds_ptr R, int m_blk, int step) {
-    typedef short v4i16 __attribute__((ext_vector_type(4)));
-    typedef short v8i16 __attribute__((ext_vector_type(8)));
+  static __device__ __forceinline__ int kmajor_base(int m_wave) {
     const int lane = opaque_tid() & 63;
     const int g = lane >> 4, c = lane & 15;
-    const int m = m_blk + 16 * (g & 1) + 4 * (c & 3);
-    const int k0 = 16 * step + 8 * (g >> 1) + (c >> 2);
+    const int m = m_wave + 16 * (g & 1) + 4 * (c & 3);
+    const int k0 = 8 * (g >> 1) + (c >> 2);
+    return k0 * PITCH + 16 * ((m >> 3) ^ swz_t(k0)) + 2 * (m & 7);
+  }
+  // kb[x]: address of the stage's base ^ 64 (x & 1) ^ 128 (x >> 1)
+  template <int PITCH>
+  static __device__ __forceinline__ bf16x8 read_kmajor(const lds_ptr (&kb)[4], int i, int step) {
+    typedef short v4i16 __attribute__((ext_vector_type(4)));
+    typedef short v8i16 __attribute__((ext_vector_type(8)));
     v4i16 h[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int k = k0 + 4 * u;
-      lds_ptr a = R + k * PITCH + 16 * ((m >> 3) ^ swz_t(k)) + 2 * (m & 7);
+      lds_ptr a = kb[(i & 1) + 2 * (((i >> 1) & 1) ^ u)] + (16 * step + 4 * u) * PITCH + 256 * (i >> 2);
       h[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) v4i16*>(a));
     }
     const v8i16 v = __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, v);
   }
+  static_assert(!PT || (WTM % (32 * FM) == 0 && (FM == 1 || FM == 2 || FM == 4)), "K-major P blocks");
+  static_assert(!QT || (!QIL_ && (FN == 1 || FN == 2 || FN == 4)), "K-major Q blocks");
 
+  // Where a wave's fragments of a stage are: byte offsets of its first P and
+  // Q row and the chunk swizzle (row-major), and the K-major bases (without
+  // the stage's address).
+  struct FragAddr {
+    int prow0, qrow0, half, sw;
+    int kp, kq;
+  };
+  static __device__ __forceinline__ FragAddr frag_addr(int wm, int wn) {
+    const int lane = opaque_tid() & 63;
+    FragAddr a;
+    a.sw = swz(lane & 31);
+    a.prow0 = (wm * WTM + (lane & 31)) * ROW_BYTES;
+    a.qrow0 = (BM + q_row(wn, 0) + (lane & 31)) * ROW_BYTES;
+    a.half = lane >> 5;
+    a.kp = PT ? kmajor_base<BM * 2>(wm * WTM) : 0;
+    a.kq = QT ? kmajor_base<BN * 2>(q_row(wn, 0)) : 0;
+    return a;
+  }
+  // the K-major bases in the stage at S
+  struct StageBase {
+    lds_ptr p[4], q[4];
+  };
+  static __device__ __forceinline__ void stage_base(lds_ptr S, const FragAddr& a, StageBase& b) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      if constexpr (PT) b.p[x] = S + (a.kp ^ (64 * (x & 1)) ^ (128 * (x >> 1)));
+      if constexpr (QT) b.q[x] = S + BM * ROW_BYTES + (a.kq ^ (64 * (x & 1)) ^ (128 * (x >> 1)));
+    }
+  }
+
+  // K step `step` of the stage at S, first NQ Q blocks.
   template <int NQ>
-  static __device__ __forceinline__ void read_step(lds_ptr S, int prow0, int qrow0, int half, int sw, int step,
+  static __device__ __forceinline__ void read_step(lds_ptr S, const StageBase& kb, const FragAddr& fa, int step,
                                                    Frags& f) {
+    const int prow0 = fa.prow0, qrow0 = fa.qrow0, half = fa.half, sw = fa.sw;
     if constexpr (NQ > 0 && F8) {
       const int c0 = 4 * step + 2 * half;
       const int o0 = (c0 ^ sw) * 16, o1 = ((c0 + 1) ^ sw) * 16;
@@ -315,9 +371,8 @@ struct GemmCore {
     } else if constexpr (NQ > 0) {
       const int pc = ((2 * step + half) ^ sw) * 16;
       if constexpr (PT) {
-        const int wm = wave_m(wave());
 #pragma unroll
-        for (int i = 0; i < FM; ++i) f.a[i] = read_kmajor<BM * 2>(S, wm * WTM + 32 * i, step);
+        for (int i = 0; i < FM; ++i) f.a[i] = read_kmajor<BM * 2>(kb.p, i, step);
       } else {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -325,9 +380,8 @@ struct GemmCore {
                                                                                       pc);
       }
       if constexpr (QT) {
-        const int wn = wave_n(wave());
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) f.b[j] = read_kmajor<BN * 2>(S + BM * ROW_BYTES, q_row(wn, j), step);
+        for (int j = 0; j < NQ; ++j) f.b[j] = read_kmajor<BN * 2>(kb.q, j, step);
       } else {
 #pragma unroll
         for (int j = 0; j < NQ; ++j)
@@ -354,7 +408,7 @@ struct GemmCore {
   // next step starts.
   template <int NQ>
   static __device__ __forceinline__ void interleave_reads() {
-    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS * (FM + NQ) : 0;
+    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS_P * FM + READS_Q * NQ : 0;
 #pragma unroll
     for (int i = 0; i < NMF; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
@@ -369,7 +423,7 @@ struct GemmCore {
   // latency is the longer one.
   template <int NQ>
   static __device__ __forceinline__ void interleave_loads() {
-    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS * (FM + NQ) : 0, NVM = LOADS;
+    constexpr int NMF = FM * NQ * MPF, NDS = NQ > 0 ? READS_P * FM + READS_Q * NQ : 0, NVM = LOADS;
     constexpr int PV = NMF < NVM ? NMF : NVM;
     constexpr int PD = (NMF - PV) < NDS ? (NMF - PV) : NDS;
 #pragma unroll
@@ -403,14 +457,14 @@ struct GemmCore {
   // Steps ST..STEPS-1 of a stage (no buffer loads): step s reads step s of
   // the stage at S into f[s & 1] while multiplying f[(s - 1) & 1].
   template <int NQ, int ST>
-  static __device__ __forceinline__ void inner_steps(lds_ptr S, int prow0, int qrow0, int half, int sw,
+  static __device__ __forceinline__ void inner_steps(lds_ptr S, const StageBase& kb, const FragAddr& fa,
                                                      Frags (&f)[2], Acc& acc, bool sched) {
     if constexpr (ST < STEPS) {
       if (sched) __builtin_amdgcn_sched_barrier(0);
-      read_step<NQ>(S, prow0, qrow0, half, sw, ST, f[ST & 1]);
+      read_step<NQ>(S, kb, fa, ST, f[ST & 1]);
       mma_step<NQ>(f[(ST - 1) & 1], acc);
       if (sched) interleave_reads<NQ>();
-      inner_steps<NQ, ST + 1>(S, prow0, qrow0, half, sw, f, acc, sched);
+      inner_steps<NQ, ST + 1>(S, kb, fa, f, acc, sched);
     }
   }
 
@@ -419,6 +473,7 @@ struct GemmCore {
     __amdgpu_buffer_rsrc_t prs, qrs;
     uint32_t goff[LOADS];
     int nk, pld, qld, kvalid;
+    int krow[2];
   };
 
   // First half of run(): issues the DMA of the tile's first min(K/BK,
@@ -439,11 +494,13 @@ struct GemmCore {
     p.qld = qld;
     p.kvalid = kvalid;
     dma_offsets(poff, qoff, pvalid, qvalid, p.goff);
+    p.krow[0] = PT ? (poff[0] == 0xFFFFFFFFu ? kNoRow : kmajor_row(SLOTS_P)) : 0;
+    p.krow[1] = QT ? (qoff[0] == 0xFFFFFFFFu ? kNoRow : kmajor_row(SLOTS_Q)) : 0;
     p.nk = __builtin_amdgcn_readfirstlane(K / BK);
     const int pro = min(p.nk, STAGES);
 #pragma unroll
     for (int s = 0; s < STAGES; ++s)
-      if (s < pro) issue(p.prs, p.qrs, p.goff, s, lds + s * STAGE_BYTES, w, pld, qld, kvalid);
+      if (s < pro) issue(p.prs, p.qrs, p.goff, s, lds + s * STAGE_BYTES, w, pld, qld, kvalid, p.krow);
   }
 
   // poff[j] (j < LP): element offset of P row load_row(j);
@@ -537,7 +594,7 @@ struct GemmCore {
     const int qrow0 = (BM + q_row(wn, 0) + (lane & 31)) * ROW_BYTES;
     const int half = lane >> 5;
     Frags f;
-    read_step<NQ>(lds, prow0, qrow0, half, sw, 0, f);
+    read_step<NQ>(lds, StageBase{}, FragAddr{prow0, qrow0, half, sw, 0, 0}, 0, f);
     int kt = 0, cb = 0;
     // steady state: stage kt+STAGES exists
     for (; kt + STAGES < nk; ++kt) {
@@ -554,7 +611,7 @@ struct GemmCore {
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): own reads of stage kt done
       raw_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      issue(prs, qrs, goff, kt + STAGES, cur, w);
+      issue(prs, qrs, goff, kt + STAGES, cur, w, 0, 0, 0x7fffffff, p.krow);
       mma_read_f8<NQ, true, LOADS>(nxt, prow0, qrow0, half, sw, 0, f, acc);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -585,11 +642,11 @@ struct GemmCore {
       return;
     }
     const lds_ptr lds = (lds_ptr)lds_generic;
-    const int lane = opaque_tid() & 63;
     const int w = wave();
     const int wm = wave_m(w), wn = wave_n(w);
     const __amdgpu_buffer_rsrc_t prs = p.prs, qrs = p.qrs;
     const int pld = p.pld, qld = p.qld, kvalid = p.kvalid;
+    const int krow[2] = {p.krow[0], p.krow[1]};
     uint32_t goff[LOADS];
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) goff[j] = p.goff[j];
@@ -597,26 +654,26 @@ struct GemmCore {
     const int pro = min(nk, STAGES);
     wait_stages(pro - 1);
     raw_barrier();
-    const int sw = swz(lane & 31);
-    const int prow0 = (wm * WTM + (lane & 31)) * ROW_BYTES;
-    const int qrow0 = (BM + q_row(wn, 0) + (lane & 31)) * ROW_BYTES;
-    const int half = lane >> 5;
+    const FragAddr fa = frag_addr(wm, wn);
+    StageBase kb;
+    stage_base(lds, fa, kb);
     Frags f[2];
-    read_step<NQ>(lds, prow0, qrow0, half, sw, 0, f[0]);
+    read_step<NQ>(lds, kb, fa, 0, f[0]);
     int kt = 0, cb = 0;   // stage and its buffer
     // steady state: stage kt+STAGES exists
     for (; kt + STAGES < nk; ++kt) {
       const lds_ptr cur = lds + cb * STAGE_BYTES;
       cb = cb + 1 == STAGES ? 0 : cb + 1;
       const lds_ptr nxt = lds + cb * STAGE_BYTES;
-      inner_steps<NQ, 1>(cur, prow0, qrow0, half, sw, f, acc, true);
+      inner_steps<NQ, 1>(cur, kb, fa, f, acc, true);
       __builtin_amdgcn_sched_barrier(0);
       wait_vmcnt<(STAGES - 2) * LOADS>();   // stage kt+1 landed (this wave's part)
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): own reads of stage kt done
       raw_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      issue(prs, qrs, goff, kt + STAGES, cur, w, pld, qld, kvalid);
-      read_step<NQ>(nxt, prow0, qrow0, half, sw, 0, f[0]);
+      issue(prs, qrs, goff, kt + STAGES, cur, w, pld, qld, kvalid, krow);
+      stage_base(nxt, fa, kb);
+      read_step<NQ>(nxt, kb, fa, 0, f[0]);
       mma_step<NQ>(f[1], acc);
       interleave_loads<NQ>();
       __builtin_amdgcn_sched_barrier(0);
@@ -625,12 +682,13 @@ struct GemmCore {
     for (; kt < nk; ++kt) {
       const lds_ptr cur = lds + cb * STAGE_BYTES;
       cb = cb + 1 == STAGES ? 0 : cb + 1;
-      inner_steps<NQ, 1>(cur, prow0, qrow0, half, sw, f, acc, false);
+      inner_steps<NQ, 1>(cur, kb, fa, f, acc, false);
       if (kt + 1 < nk) {
         wait_stages(nk - 2 - kt);
         __builtin_amdgcn_s_waitcnt(0xC07F);
         raw_barrier();
-        read_step<NQ>(lds + cb * STAGE_BYTES, prow0, qrow0, half, sw, 0, f[0]);
+        stage_base(lds + cb * STAGE_BYTES, fa, kb);
+        read_step<NQ>(lds + cb * STAGE_BYTES, kb, fa, 0, f[0]);
       }
       mma_step<NQ>(f[1], acc);
     }
