@@ -180,17 +180,19 @@ int luffy_condense(const void* x, int T, int d, int dtype,
                    void* workspace, size_t workspace_bytes, void* stream);
 
 /* ------------------------------------------------------------------------
- * Similarity screen of luffy_condense (bf16 calls with d >= 2048, d a
- * multiple of 128 and T*k >= 512*E; not luffy_condense_history).  The
+ * Similarity screen of luffy_condense (bf16 calls with d >= 2048 and
+ * T*k >= 512*E; not luffy_condense_history).  The
  * cosines of Sec. 5.1 are first estimated on fp8 (E4M3) copies of the rows,
- * each scaled by a power of two, with a bound derived from every row's
+ * each normalised, with a bound derived from every row's
  * quantisation error: |c~ - c| <= rho_a + rho_b + rho_a*rho_b (plus room for
- * float32 rounding), rho = |x - x^| / |x|.  A 256 x 256 tile whose every
- * estimate lies outside that band around the threshold is decided by the
- * estimates, which then agree with the exact comparison for every pair; any
- * other tile is recomputed from the bf16 rows.  The outputs are the same
- * with the screen on or off.  The workspace of such calls holds the fp8
- * rows (T*d bytes).
+ * float32 rounding), rho = |x - x^| / |x|; over the first values of the rows
+ * alone the rest adds at most the product of what the two rows keep there.  A
+ * pair whose bound stays on one side of the threshold is decided, which then
+ * agrees with the exact comparison; a tile's few other pairs are decided by
+ * their own dot products, and a 256 x 256 tile with many of them, or with one
+ * within float32 rounding of the threshold, is recomputed from the bf16 rows.
+ * The outputs are the same with the screen on or off.  The workspace of such
+ * calls holds the fp8 rows (T+1 rows of d rounded up to 128 bytes).
  *
  * luffy_set_similarity_screen  on != 0 enables the screen (the default),
  *                              0 disables it for later calls in this

@@ -5,6 +5,8 @@
 //   norm_kernel          1/|x_t| per token (one wave per row); clears the
 //                        degree counters and walk states; its first wave
 //                        lays out every bucket's tiles and bitmask.
+//   gram_screen_kernel   (long bf16 rows, large buckets) the tiles below decided
+//                        from fp8 products and a few single ones.
 //   gram_kernel_{bf16,f32}  persistent loop over the upper-triangle tiles
 //                        (256 rows bf16, 64 rows fp32) of every bucket's Gram
 //                        matrix.  The epilogue turns cos >= h into adjacency
@@ -108,27 +110,37 @@ __device__ __forceinline__ void gram_layout(const int32_t* __restrict__ offsets,
 // 256 (|x_n| = 256 up to the rounding of the norm, every value within
 // +-256, inside the E4M3 range), rounded to E4M3 by the hardware conversion
 // (values below the smallest normal, 2^-6, stored as 0, so no subnormal
-// reaches the MFMA).  rho[t] = |x_n - x^| / |x_n| is taken from the decoded
-// bytes, i.e. from the values the MFMA multiplies, and enlarged by 2^-9 to
-// cover the float32 sums.  Then for every pair c~ = x^_a . x^_b / 2^16 (the
-// raw fp8 product scaled by a power of two) and the cosine c of the bf16
-// pass satisfy
+// reaches the MFMA).  Rows are padded with zeros to dp values, a multiple of
+// 128.  rowq[t] holds, all relative to |x_n| and taken from the decoded bytes,
+// i.e. from the values the MFMA multiplies,
+//   x  rho, the row's quantisation error |x_n - x^|,
+//   y  the same over its first da values,
+//   z  |x_n| over the values from da on (the part a product of the first da
+//      values leaves out),
+// each enlarged a little to cover the float32 sums.  Then for every pair
+// c~ = x^_a . x^_b / 2^16 (the raw fp8 product scaled by a power of two) and
+// the cosine c of the bf16 pass satisfy
 //   |c - c~| <= (|x^_a| |e_b| + |e_a| |x_b|) / (|x_a| |x_b|) <= rho_a + rho_b + rho_a rho_b
-// (e = x_n - x^, |x_n| = 256), up to float32 rounding.  Row T of x8 (the
-// pad row of partial tiles) is zero.  One wave a row (norm_kernel's QUANT
-// pass); d % 8 == 0.
+// (e = x_n - x^, |x_n| = 256), up to float32 rounding; over the first da values
+// alone the same holds with y for x, and the rest adds at most z_a z_b
+// (Cauchy-Schwarz).  Row T of x8 (the pad row of partial tiles) is zero.  One
+// wave a row (norm_kernel's QUANT pass); d and da are multiples of 64.
 __device__ __forceinline__ void gram_quant_row(const uint16_t* __restrict__ x, int T, int d, int t, float inv,
-                                               uint8_t* __restrict__ x8, float* __restrict__ rho) {
+                                               int dp, int da, uint8_t* __restrict__ x8, float4* __restrict__ rowq) {
   const int lane = threadIdx.x & 63;
-  uint8_t* out = x8 + static_cast<size_t>(t) * d;
+  uint8_t* out = x8 + static_cast<size_t>(t) * dp;
   if (t == T) {
-    for (int c = lane * 8; c < d; c += 512) *reinterpret_cast<uint2*>(out + c) = make_uint2(0u, 0u);
+    for (int c = lane * 8; c < dp; c += 512) *reinterpret_cast<uint2*>(out + c) = make_uint2(0u, 0u);
     return;
   }
   const uint16_t* row = x + static_cast<size_t>(t) * d;
   const float sc = inv * 256.f;
-  float se = 0.f, sx = 0.f;
-  for (int c = lane * 8; c < d; c += 512) {
+  float se = 0.f, sx = 0.f, sea = 0.f, sxb = 0.f;   // error and square sums; error of the first da, squares of the rest
+  for (int c = lane * 8; c < dp; c += 512) {
+    if (c >= d) {
+      *reinterpret_cast<uint2*>(out + c) = make_uint2(0u, 0u);
+      continue;
+    }
     Pack16 v;
     v.u4 = *reinterpret_cast<const uint4*>(row + c);
     float f[8], g[8];
@@ -146,16 +158,27 @@ __device__ __forceinline__ void gram_quant_row(const uint16_t* __restrict__ x, i
                          __builtin_amdgcn_cvt_f32_fp8(lo, 2), __builtin_amdgcn_cvt_f32_fp8(lo, 3),
                          __builtin_amdgcn_cvt_f32_fp8(hi, 0), __builtin_amdgcn_cvt_f32_fp8(hi, 1),
                          __builtin_amdgcn_cvt_f32_fp8(hi, 2), __builtin_amdgcn_cvt_f32_fp8(hi, 3)};
+    float e8 = 0.f, x8s = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float df = f[i] - dq[i];
-      se = fmaf(df, df, se);
-      sx = fmaf(f[i], f[i], sx);
+      e8 = fmaf(df, df, e8);
+      x8s = fmaf(f[i], f[i], x8s);
     }
+    se += e8;
+    sx += x8s;
+    if (c < da) sea += e8;
+    else sxb += x8s;
   }
   se = wave_sum_f32(se);
   sx = wave_sum_f32(sx);
-  if (lane == 0) rho[t] = sx > 0.f ? sqrtf(se / sx) * (1.f + 0x1p-9f) : 0.f;
+  sea = wave_sum_f32(sea);
+  sxb = wave_sum_f32(sxb);
+  if (lane == 0) {
+    constexpr float kUp = 1.f + 0x1p-9f;
+    rowq[t] = sx > 0.f ? make_float4(sqrtf(se / sx) * kUp, sqrtf(sea / sx) * kUp, sqrtf(sxb / sx) * kUp, 0.f)
+                       : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
 }
 
 // NORMS = false: the norms were computed by the caller (luffy_route); only
@@ -170,8 +193,8 @@ __global__ __launch_bounds__(256) void norm_kernel(const void* __restrict__ xv, 
                                                    int tile, long long cap_words, int32_t* __restrict__ tile_off,
                                                    long long* __restrict__ bm_off, int* __restrict__ err,
                                                    unsigned long long* __restrict__ stats, int* __restrict__ queue,
-                                                   int* __restrict__ left, int* __restrict__ list_count,
-                                                   uint8_t* __restrict__ x8, float* __restrict__ rho) {
+                                                   int* __restrict__ left, int* __restrict__ list_count, int dp,
+                                                   int da, uint8_t* __restrict__ x8, float4* __restrict__ rowq) {
   if (blockIdx.x == 0 && threadIdx.x < 64)
     gram_layout(offsets, E, max_bucket, tile, cap_words, tile_off, bm_off, err);
   if (stats && blockIdx.x == 0 && threadIdx.x >= 64 && threadIdx.x < 68) stats[threadIdx.x - 64] = 0ull;
@@ -190,10 +213,10 @@ __global__ __launch_bounds__(256) void norm_kernel(const void* __restrict__ xv, 
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if constexpr (QUANT) {
     static_assert(BF16, "fp8 rows of bf16 tokens");
-    if (t == T) gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, 0.f, x8, rho);
+    if (t == T) gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, 0.f, dp, da, x8, rowq);
     if (t >= T) return;
     if constexpr (!NORMS) {
-      gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, inv_norm[t], x8, rho);
+      gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, inv_norm[t], dp, da, x8, rowq);
       return;
     }
   }
@@ -223,7 +246,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const void* __restrict__ xv, 
   s = wave_sum_f32(s);
   const float inv = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
   if (lane == 0) inv_norm[t] = inv;
-  if constexpr (QUANT) gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, inv, x8, rho);
+  if constexpr (QUANT) gram_quant_row(static_cast<const uint16_t*>(xv), T, d, t, inv, dp, da, x8, rowq);
 }
 
 struct TileCoord {
@@ -249,10 +272,10 @@ __device__ __forceinline__ void locate_bucket_from(int tile, int to, int o0, int
                                                    int& lo, int& n) {
   const int lane = threadIdx.x & 63;
   const bool in = lane < E;
-  e = __popcll(__ballot(in && lane >= 1 && to <= tile));
-  tbase = __builtin_amdgcn_readfirstlane(__shfl(to, e, 64));
-  lo = __builtin_amdgcn_readfirstlane(__shfl(o0, e, 64));
-  n = __builtin_amdgcn_readfirstlane(__shfl(o1, e, 64)) - lo;
+  e = __popcll(__ballot(in && lane >= 1 && to <= tile));   // wave-uniform, at most E - 1
+  tbase = __builtin_amdgcn_readlane(to, e);
+  lo = __builtin_amdgcn_readlane(o0, e);
+  n = __builtin_amdgcn_readlane(o1, e) - lo;
 }
 
 __device__ __forceinline__ void locate_bucket(int tile, const int32_t* __restrict__ tile_off,
@@ -473,12 +496,70 @@ __device__ __forceinline__ uint32_t transpose32_bits(uint32_t x) {
   return transpose_step<1>(x, i);
 }
 
-// Modes of the bf16 similarity kernel: every tile on bf16 MFMA; every tile
-// on fp8 MFMA as a screen; the bf16 pass over the tiles the screen left.
-enum GramMode { kGramPlain = 0, kGramScreen = 1, kGramList = 2 };
+// Writes a 256 x 256 tile's adjacency words (4 per row, direct and, off the
+// diagonal, mirrored) and adds each row's edge count to its degree, from the
+// tile's bit pieces dbits[row][32-column group], tbits[column][32-row group].
+__device__ __forceinline__ void write_gram_tile(const TileCoord& c, const uint32_t (*dbits)[kTile / 32],
+                                                const uint32_t (*tbits)[kTile / 32], uint64_t* __restrict__ bitmask,
+                                                long long base, int32_t* __restrict__ deg, int threads) {
+  // degree: edges of each tile row (and, off the diagonal, of each mirrored row)
+  for (int i = opaque_tid(); i < 2 * kTile; i += threads) {
+    const bool mirror = i >= kTile;
+    const int rl = mirror ? i - kTile : i;
+    const uint32_t* pcs = mirror ? tbits[rl] : dbits[rl];
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < kTile / 32; ++g) cnt += __popc(pcs[g]);
+    const int r = (mirror ? c.tj : c.ti) * kTile + rl;
+    if (cnt && r < c.n && (!mirror || c.ti != c.tj)) atomicAdd(&deg[c.lo + r], cnt);
+  }
+  // two words a thread
+  auto store2 = [&](const uint32_t* pcs, int row, int wd) {
+    if (row >= c.n || wd >= c.W) return;
+    const uint4 v = *reinterpret_cast<const uint4*>(pcs);
+    uint64_t* dst = bitmask + base + static_cast<long long>(row) * c.W + wd;
+    if (wd + 1 < c.W) {
+      __builtin_memcpy(dst, &v, 16);
+    } else {
+      const uint64_t lo = static_cast<uint64_t>(v.x) | (static_cast<uint64_t>(v.y) << 32);
+      *dst = lo;
+    }
+  };
+  for (int i = opaque_tid(); i < kTile * 2; i += threads) {
+    const int rl = i >> 1, ww = 2 * (i & 1);
+    store2(&dbits[rl][2 * ww], c.ti * kTile + rl, 4 * c.tj + ww);
+    if (c.ti != c.tj) store2(&tbits[rl][2 * ww], c.tj * kTile + rl, 4 * c.ti + ww);
+  }
+}
 
-// Persistent over the upper-triangle tiles of every bucket.  The loop is
-// software-pipelined across tiles: the next tile's bucket lookup is loaded
+// Column piece of a 32 x 32 block from a lane's 16 compare bits (bit v:
+// accumulator v, row 8 (v / 4) + v % 4 + 4 (l / 32)): the bits spread to their
+// rows and the two half-waves merged; a token with itself is dropped on a
+// diagonal block.
+__device__ __forceinline__ uint32_t spread_col_bits(uint32_t bits, int hi, bool diag, int l31) {
+  // nibble k (accumulators 4k..4k+3) to bits 8k..8k+3, then this half's rows
+  bits = (bits & 0xFFu) | ((bits & 0xFF00u) << 8);
+  bits = (bits & 0x000F000Fu) | ((bits & 0x00F000F0u) << 4);
+  bits <<= 4 * hi;
+  uint32_t cw = bits | static_cast<uint32_t>(__shfl_xor(static_cast<int>(bits), 32, 64));
+  if (diag) cw &= ~(1u << l31);
+  return cw;
+}
+
+// Row pieces of a wave's pair of column blocks (bit transposes of their
+// column pieces, one block per half-wave), stored at d[row][group].
+__device__ __forceinline__ void store_row_bits(uint32_t col0, uint32_t col1, int hi, int l31, int abase, int bbase,
+                                               uint32_t (*dbits)[kTile / 32]) {
+  // lower half-wave: the first block, upper: the second (a select, not an
+  // indexed read, which would put the words in memory)
+  const uint32_t sel = col0 ^ ((col0 ^ col1) & (0u - static_cast<uint32_t>(hi)));
+  const uint32_t rowbits = transpose32_bits(sel);
+  dbits[abase + l31][(bbase + 32 * hi) >> 5] = rowbits;
+}
+
+// Similarity tiles on bf16 MFMA.  LIST = false: every upper-triangle tile of
+// every bucket; LIST = true: the tiles the screen handed back.  The tile loop
+// is software-pipelined: the next tile's bucket lookup is loaded
 // before the current tile's K loop (nothing waits on it until the loop is
 // over, so it does not hold up the loop's first stages, which the in-order
 // load counter would otherwise tie to it); right after the K loop the next
@@ -486,84 +567,52 @@ enum GramMode { kGramPlain = 0, kGramScreen = 1, kGramList = 2 };
 // compares, and its first DMA stages are issued before the rest of this
 // tile's epilogue, which therefore keeps its bit pieces outside the operand
 // ring.
-//
-// kGramScreen (h > 0): X holds the fp8 rows (E4M3 unit rows scaled by 2^8,
-// rows of d_units 16-bit units; row T_pad is zero and stands in for the
-// rows past a bucket), so a tile's products are 2^16 c~, estimates of the
-// cosines with |c~ - c| <= band for every pair: band = 2 r + r^2 + 4e-3, r
-// the largest rho (quantisation error, see gram_quant_row) of the
-// tile's rows, the constant room for the float32 rounding of both passes.
-// A tile whose every value lies outside (h - band, h + band) is decided
-// exactly by c~ >= h: it is written as in the bf16 pass.  Any other tile is
-// appended to `list` (count in list_count) and leaves its words and degrees
-// to the kGramList pass, which recomputes it from the bf16 rows.
-template <int MODE>
+template <bool LIST>
 __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
-    const uint16_t* __restrict__ X, int d_units, const int32_t* __restrict__ perm_token,
+    const uint16_t* __restrict__ X, int d, const int32_t* __restrict__ perm_token,
     const int32_t* __restrict__ offsets, int E, const float* __restrict__ inv_norm, float h,
     const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off,
     const int* __restrict__ err, uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg,
-    const float* __restrict__ rho, int* __restrict__ list, int* __restrict__ list_count, int T_pad) {
-  using G = std::conditional_t<MODE == kGramScreen, GemmBig64F8, GramGemm>;
-  static_assert(G::BM == kTile && G::BN == kTile && G::THREADS == GramGemm::THREADS, "similarity tile");
+    const int* __restrict__ list, const int* __restrict__ list_count) {
+  using G = GramGemm;
   constexpr int NI = 2 * kTile / G::THREADS;   // inverse norms staged per thread
-  static_assert(G::FN % 2 == 0, "column blocks are transposed in pairs");
+  static_assert(G::FN == 2, "column blocks are transposed in pairs");
   // One LDS array: the operand ring, then the inverse norms of the tile's P
   // rows (0..kTile-1) and Q rows (kTile..), then the tile's adjacency
-  // pieces, dbits[row][32-column group] and tbits[column][32-row group],
-  // then the screen's flag.  With separate LDS variables the compiler loses
+  // pieces.  With separate LDS variables the compiler loses
   // the alias scopes that tell a stage's fragment reads from the DMA into
   // the other stage, and waits for each stage's DMA right after issuing it
   // (no overlap).
   constexpr int kInvOff = G::LDS_BYTES, kBitsOff = kInvOff + 2 * kTile * 4;
-  constexpr int kRhoOff = kBitsOff + 2 * kTile * (kTile / 32) * 4;
-  constexpr int kFlagOff = kRhoOff + (MODE == kGramScreen ? 2 * kTile * 4 : 0);
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kFlagOff + 16];
-  float* rho_ab = reinterpret_cast<float*>(lds + kRhoOff);   // the screen's rho of the P and Q rows
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kBitsOff + 2 * kTile * (kTile / 32) * 4];
   float* inv_ab = reinterpret_cast<float*>(lds + kInvOff);
   uint32_t (*dbits)[kTile / 32] = reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + kBitsOff);
   uint32_t (*tbits)[kTile / 32] = reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + kBitsOff + kTile * (kTile / 32) * 4);
-  int* flag = reinterpret_cast<int*>(lds + kFlagOff);
   const float* inv_a = inv_ab;
   const float* inv_b = inv_ab + kTile;
   if (*err) return;
   const int w = G::wave();
   const int wm = G::wave_m(w), wn = G::wave_n(w);
-  // items: tiles 0..total-1, or the listed ones
-  const int total = MODE == kGramList ? *list_count : tile_off[E];
-  auto tile_of = [&](int item) { return MODE == kGramList ? list[item] : item; };
+  const int total = LIST ? *list_count : tile_off[E];
+  auto tile_of = [&](int item) { return LIST ? list[item] : item; };
   int item = xcd_virtual_block();
   if (item >= total) return;   // block-uniform, before any barrier
-  int tile = tile_of(item);
-  TileCoord c = decode_tile_grouped(tile, tile_off, offsets, E);
+  TileCoord c = decode_tile_grouped(tile_of(item), tile_off, offsets, E);
   int32_t ptok[G::LP], qtok[G::LQ], itok[NI];
   uint32_t poff[G::LP], qoff[G::LQ];
-  // the screen's rows past the bucket read the zero row T (x8 has T + 1)
-  constexpr bool SCR = MODE == kGramScreen;
-  const int pad = SCR ? T_pad : -1;
-  gram_tile_tokens<G>(c, perm_token, ptok, qtok, itok, pad);
+  gram_tile_tokens<G>(c, perm_token, ptok, qtok, itok);
 #pragma unroll
-  for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(ptok[j]) * d_units;
+  for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(ptok[j]) * d;
 #pragma unroll
-  for (int j = 0; j < G::LQ; ++j) qoff[j] = static_cast<uint32_t>(qtok[j]) * d_units;
-  float inv[NI], rh[NI];
+  for (int j = 0; j < G::LQ; ++j) qoff[j] = static_cast<uint32_t>(qtok[j]) * d;
+  float inv[NI];
 #pragma unroll
-  for (int u = 0; u < NI; ++u) {
-    if constexpr (SCR) rh[u] = itok[u] >= 0 ? rho[itok[u]] : 0.f;
-    else inv[u] = gram_stage_inv(inv_norm, itok[u]);
-  }
+  for (int u = 0; u < NI; ++u) inv[u] = gram_stage_inv(inv_norm, itok[u]);
   typename G::Pipe pipe;
-  G::prefetch(X, poff, X, qoff, d_units, SCR ? kTile : c.n - c.ti * kTile, SCR ? kTile : c.n - c.tj * kTile, lds,
-              pipe);
+  G::prefetch(X, poff, X, qoff, d, c.n - c.ti * kTile, c.n - c.tj * kTile, lds, pipe);
   for (;;) {
-    if constexpr (!SCR) {
 #pragma unroll
-      for (int u = 0; u < NI; ++u) inv_ab[opaque_tid() + u * G::THREADS] = inv[u];   // visible after the K loop's first barrier
-    } else {
-#pragma unroll
-      for (int u = 0; u < NI; ++u) rho_ab[opaque_tid() + u * G::THREADS] = rh[u];
-      if (opaque_tid() == 0) *flag = 0;   // likewise; every wave read the last tile's flag before the loop's barrier
-    }
+    for (int u = 0; u < NI; ++u) inv_ab[opaque_tid() + u * G::THREADS] = inv[u];   // visible after the K loop's first barrier
     const int nitem = item + gridDim.x;
     const int next = nitem < total ? tile_of(nitem) : 0;
     int nto = 0, no0 = 0, no1 = 0;
@@ -574,7 +623,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
     TileCoord cn = c;
     if (nitem < total) {
       cn = decode_tile_grouped_from(next, nto, no0, no1, E);
-      gram_tile_tokens<G>(cn, perm_token, ptok, qtok, itok, pad);
+      gram_tile_tokens<G>(cn, perm_token, ptok, qtok, itok);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -587,41 +636,24 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
     // column pieces: the two column blocks of a wave are transposed
     // together, one per half-wave.  Edge test: dot * (1/|a|) * (1/|b|) >= h
     // (rows outside the bucket carry a NaN scale), never a token with
-    // itself.  The screen tests its product against 2^16 h (its rows past
-    // the bucket are zero: no edge for h > 0) and also keeps the least
-    // |product - 2^16 h| of the lane.
+    // itself.
     // lane values recomputed from the opaque thread index: hoisted out of
     // the tile loop they would stay live across the K loop
     const int el = opaque_tid() & 63;
     const int l31 = el & 31, hi = el >> 5;
     const bool same_tile = c.ti == c.tj;
-    float dmin = __builtin_inff(), band = 0.f;
-    if constexpr (MODE == kGramScreen) {
-      // |c~ - c| <= rho_a + rho_b + rho_a rho_b over the tile's rows
-      float r = 0.f;
-#pragma unroll
-      for (int q = 0; q < 2 * kTile / 256; ++q) {
-        const float4 f = *reinterpret_cast<const float4*>(&rho_ab[256 * q + 4 * el]);
-        r = fmaxf(r, fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)));
-      }
-      for (int o = 32; o >= 1; o >>= 1) r = fmaxf(r, __shfl_xor(r, o, 64));
-      band = (2.f * r + r * r + 4e-3f) * 65536.f;
-    }
-    const float hs = h * 65536.f;   // the threshold in units of the screen's products (exact)
 #pragma unroll
     for (int fm = 0; fm < G::FM; ++fm) {
       const int abase = wm * G::WTM + 32 * fm;
       // this lane's 16 rows: abase + 8q + 4hi + r, as 4 runs of 4
       float ia[16];
-      if constexpr (!SCR) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 f = *reinterpret_cast<const float4*>(&inv_a[abase + 8 * q + 4 * hi]);
-          ia[4 * q] = f.x;
-          ia[4 * q + 1] = f.y;
-          ia[4 * q + 2] = f.z;
-          ia[4 * q + 3] = f.w;
-        }
+      for (int q = 0; q < 4; ++q) {
+        const float4 f = *reinterpret_cast<const float4*>(&inv_a[abase + 8 * q + 4 * hi]);
+        ia[4 * q] = f.x;
+        ia[4 * q + 1] = f.y;
+        ia[4 * q + 2] = f.z;
+        ia[4 * q + 3] = f.w;
       }
       uint32_t col[G::FN];
 #pragma unroll
@@ -629,10 +661,324 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
         const int bbase = wn * G::WTN + 32 * fn;
         const int bl = bbase + l31;
         uint32_t bits = 0;
-        if constexpr (SCR) {
-          // raw fp8 products of unit rows scaled by 2^8: c~ = acc / 2^16;
-          // a token with itself is set to 0 (no edge for h > 0, and it
-          // stays out of the band; the word drops it below anyway)
+        const float ib = inv_b[bl];
+        float p = acc[fm][fn][15] * ia[15] * ib;
+#pragma unroll
+        for (int v = 15; v >= 1; --v) {
+          float q;
+          bits = shift_in_ge_next(bits, p, h, acc[fm][fn][v - 1], ia[v - 1], ib, q);
+          p = q;
+        }
+        bits = shift_in_ge_last(bits, p, h);
+        col[fn] = spread_col_bits(bits, hi, same_tile && abase == bbase, l31);
+        if (hi == 0) tbits[bl][abase >> 5] = col[fn];
+      }
+      store_row_bits(col[0], col[1], hi, l31, abase, wn * G::WTN, dbits);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (nitem < total) {
+#pragma unroll
+      for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(ptok[j]) * d;
+#pragma unroll
+      for (int j = 0; j < G::LQ; ++j) qoff[j] = static_cast<uint32_t>(qtok[j]) * d;
+      // before the DMA: waiting for them then does not wait for the DMA
+#pragma unroll
+      for (int u = 0; u < NI; ++u) inv[u] = gram_stage_inv(inv_norm, itok[u]);
+      G::prefetch(X, poff, X, qoff, d, cn.n - cn.ti * kTile, cn.n - cn.tj * kTile, lds, pipe);
+    }
+    // LDS-only barriers from here on: a full __syncthreads() would also wait
+    // for the next tile's DMA
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's pieces are in LDS
+    raw_barrier();
+    write_gram_tile(c, dbits, tbits, bitmask, bm_off[c.e], deg, G::THREADS);
+    if (nitem >= total) break;
+    // every wave's reads of the pieces and of inv_ab are done before the next
+    // tile overwrites them
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    raw_barrier();
+    item = nitem;
+    c = cn;
+  }
+}
+
+// The similarity screen's arguments.
+struct ScreenArgs {
+  const uint8_t* x8;      // fp8 rows (E4M3, scaled by 2^8), pitch dp; row T is zero
+  const float4* rowq;     // error bounds of every row (gram_quant_row)
+  const uint16_t* x;      // the bf16 rows
+  const float* inv_norm;
+  int d, dp, da, T;
+  float h;                // > 0
+  int* list;              // tiles handed back to the bf16 pass
+  int* list_count;
+};
+
+constexpr int kWavePairs = 64;    // pairs of a wave's part of a tile that can be looked at one by one
+constexpr int kWaveFirst = 32;    // of them after the first da values
+
+// Wave-wide maximum and sum, the same in every lane: DPP rotations inside the
+// rows of 16, then the four rows read as scalars (a cross-lane shuffle through
+// LDS per step would take six dependent LDS round trips).
+template <int N>
+__device__ __forceinline__ float row_rotate(float x) {
+  return __uint_as_float(static_cast<uint32_t>(
+      __builtin_amdgcn_update_dpp(0, static_cast<int>(__float_as_uint(x)), 0x120 + N, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float lane_value(float x, int l) {
+  return __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(x)), l)));
+}
+__device__ __forceinline__ float wave_max_dpp(float x) {
+  x = fmaxf(x, row_rotate<8>(x));
+  x = fmaxf(x, row_rotate<4>(x));
+  x = fmaxf(x, row_rotate<2>(x));
+  x = fmaxf(x, row_rotate<1>(x));
+  return fmaxf(fmaxf(lane_value(x, 0), lane_value(x, 16)), fmaxf(lane_value(x, 32), lane_value(x, 48)));
+}
+__device__ __forceinline__ float wave_sum_dpp(float x) {
+  x += row_rotate<8>(x);
+  x += row_rotate<4>(x);
+  x += row_rotate<2>(x);
+  x += row_rotate<1>(x);
+  return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
+}
+
+// The similarity screen: every upper-triangle tile decided from fp8 products
+// where their error bound allows it, and from single products of two rows where
+// a few pairs of it are too close.  The result is the one of the bf16 pass.
+//
+// Phase 1 multiplies only the first da values of the rows (ScreenArgs.da < dp).
+// With c~ the estimate over them, a pair's cosine is below
+// c~ + band + z_a z_b (band: the quantisation bound; z: what the rows keep
+// beyond da), so a pair with c~ < h - band - max z max z is no edge.  Tokens of
+// different meaning are nearly orthogonal, so what is left is little more than
+// the tile's edges themselves (an expert's bucket of n tokens in groups of g
+// has about 65536 (g - 1) / n of them per tile).  Each wave keeps the pairs left
+// of its part of the tile; if no wave has more than kWaveFirst, every wave adds
+// the rest of its pairs' fp8 products one pair at a time.  Otherwise phase 2
+// multiplies the rest of the values for the whole tile.  Either way a pair whose
+// full estimate is further than band from h is decided, and a closer one gets
+// its bf16 dot product.  A tile where a wave has more than kWavePairs of those,
+// or one whose dot product is within float32 rounding of h, is listed for the
+// bf16 pass and not written.
+//
+// Why: a whole fp8 tile is bound by its K loop (LDS traffic and MFMA issue,
+// 2,670 cycles per 128 values) and the compares of its 65536 results; the first
+// 512 of 2048 values leave about 55 pairs of a tile of the expert-parallel
+// share (T = 32768, d = 2048, h = 0.9).
+// That layer's similarity: whole fp8 products 519 us, this 328; 16384 i.i.d.
+// tokens of d = 4096: 111 -> 46 us.
+__global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
+    ScreenArgs sa, const int32_t* __restrict__ perm_token, const int32_t* __restrict__ offsets, int E,
+    const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off, const int* __restrict__ err,
+    uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg) {
+  using G = GemmBig64F8;
+  static_assert(G::BM == kTile && G::BN == kTile && G::THREADS == 2 * kTile && G::NWAVES == 8, "one row a thread");
+  // one LDS array (see gram_kernel_bf16): the operand ring, the waves' row
+  // bounds, the tokens of this tile and of the next (P rows, then Q rows), the
+  // adjacency pieces, the bucket tables, every wave's pairs (row << 8 | column,
+  // then their estimates so far), every wave's pairs still too close after
+  // their whole fp8 product, the pair counts and the hand-back flag
+  constexpr int kRedOff = G::LDS_BYTES, kTokOff = kRedOff + G::NWAVES * 16, kBitsOff = kTokOff + 4 * kTile * 4;
+  constexpr int kTabOff = kBitsOff + 2 * kTile * (kTile / 32) * 4, kListOff = kTabOff + 3 * kMaxExperts * 4;
+  constexpr int kCloseOff = kListOff + G::NWAVES * kWavePairs * 8, kCntOff = kCloseOff + G::NWAVES * kWavePairs * 4;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kCntOff + 48];
+  float4* red = reinterpret_cast<float4*>(lds + kRedOff);
+  uint32_t (*dbits)[kTile / 32] = reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + kBitsOff);
+  uint32_t (*tbits)[kTile / 32] = reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + kBitsOff + kTile * (kTile / 32) * 4);
+  int* tab = reinterpret_cast<int*>(lds + kTabOff);
+  int* cnt = reinterpret_cast<int*>(lds + kCntOff);   // [w]: pairs of wave w; [8]: hand the tile back
+  if (*err) return;
+  const int w = G::wave();
+  const int wm = G::wave_m(w), wn = G::wave_n(w);
+  const int total = tile_off[E];
+  int tile = xcd_virtual_block();
+  if (tile >= total) return;   // block-uniform, before any barrier
+  const uint16_t* X = reinterpret_cast<const uint16_t*>(sa.x8);
+  const int K = sa.dp / 2, KA = sa.da / 2;   // 16-bit units, 64 a stage
+  const bool two = KA < K;
+  if (w == 0) {
+    int to, o0, o1;
+    bucket_lookup_loads(tile_off, offsets, E, to, o0, o1);
+    const int l = opaque_tid();
+    tab[l] = to;
+    tab[kMaxExperts + l] = o0;
+    tab[2 * kMaxExperts + l] = o1;
+  }
+  __syncthreads();
+  auto decode = [&](int t) {
+    const int l = opaque_tid() & 63;
+    return decode_tile_grouped_from(t, tab[l], tab[kMaxExperts + l], tab[2 * kMaxExperts + l], E);
+  };
+  auto tokens = [&](int buf) { return reinterpret_cast<int32_t*>(lds + kTokOff) + buf * 2 * kTile; };
+  // tokens of the tile's rows straight to LDS: wave w takes rows 64 (w % 4) .. of
+  // P (w < 4) or Q; rows past the bucket repeat its last one
+  auto fetch_tokens = [&](const TileCoord& t, int buf) {
+    const int l = opaque_tid() & 63;
+    const int r = (w < 4 ? t.ti : t.tj) * kTile + 64 * (w & 3) + l;
+    const uint32_t off = static_cast<uint32_t>(t.lo + min(r, t.n - 1)) * 4u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        G::rsrc(perm_token),
+        reinterpret_cast<__attribute__((address_space(3))) void*>((G::lds_ptr)(lds + kTokOff) + (buf * 2 * kTile + 64 * w) * 4),
+        4, off, 0, 0, 0);
+  };
+  // row offsets of the tile's DMA (the zero row past the bucket) over nk units
+  // from unit k0 on
+  typename G::Pipe pipe;
+  auto prepare = [&](const TileCoord& t, int buf, int k0, int nk) {
+    const int32_t* tk = tokens(buf);
+    uint32_t poff[G::LP], qoff[G::LQ];
+#pragma unroll
+    for (int j = 0; j < G::LP; ++j) {
+      const int r = G::load_row(j);
+      poff[j] = static_cast<uint32_t>(t.ti * kTile + r < t.n ? tk[r] : sa.T) * K;
+    }
+#pragma unroll
+    for (int j = 0; j < G::LQ; ++j) {
+      const int r = G::load_row(G::LP + j) - G::BM;
+      qoff[j] = static_cast<uint32_t>(t.tj * kTile + r < t.n ? tk[kTile + r] : sa.T) * K;
+    }
+    G::prepare(X + k0, poff, X + k0, qoff, nk, kTile, kTile, pipe);
+  };
+  constexpr int kDma = G::STAGES * G::LOADS;   // loads of a tile's first stages
+  // the same with the first stages issued
+  auto start = [&](const TileCoord& t, int buf, int k0, int nk) {
+    prepare(t, buf, k0, nk);
+#pragma unroll
+    for (int i = 0; i < kDma; ++i) G::issue_one(pipe, i, lds);
+  };
+  // error bounds of this thread's row (thread i: P row i, then Q row i - 256)
+  auto bounds = [&](const TileCoord& t, int buf) {
+    const int i = opaque_tid();
+    const int r = (i < kTile ? t.ti : t.tj - 1) * kTile + i;
+    return r < t.n ? sa.rowq[tokens(buf)[i]] : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  TileCoord c = decode(tile);
+  fetch_tokens(c, 0);
+  __syncthreads();   // (waits for the DMA too)
+  float4 rq = bounds(c, 0);
+  start(c, 0, 0, KA);
+  const float hs = sa.h * 65536.f;   // the threshold in units of the fp8 products (exact)
+  for (int buf = 0;; buf ^= 1) {
+    const int ntile = tile + gridDim.x;
+    const bool more = ntile < total;
+    TileCoord cn = c;
+    if (more) {
+      cn = decode(ntile);
+      fetch_tokens(cn, buf ^ 1);   // lands under the K loop
+    }
+    // staged for this tile, visible after the K loop's barriers
+    {
+      const float4 m = make_float4(wave_max_dpp(rq.x), wave_max_dpp(rq.y), wave_max_dpp(rq.z), 0.f);
+      const int tid = opaque_tid();
+      if ((tid & 63) == 0) red[w] = m;
+      if (tid == 0) cnt[8] = 0;
+      uint4* z = reinterpret_cast<uint4*>(&dbits[0][0]);
+      z[tid] = z[tid + G::THREADS] = make_uint4(0u, 0u, 0u, 0u);
+      static_assert(2 * G::THREADS * 16 == 2 * kTile * (kTile / 32) * 4, "cleared pieces");
+    }
+    typename G::Acc acc;
+    G::zero(acc);
+    G::resume(pipe, lds, acc);   // ends with a barrier: the ring is free
+    if (more) {
+      // the next tile's first stages are issued between this tile's compares
+      // and land under the rest of its epilogue
+      rq = bounds(cn, buf ^ 1);
+      prepare(cn, buf ^ 1, 0, KA);
+      if (!two) {
+#pragma unroll
+        for (int i = 0; i < kDma; ++i) G::issue_one(pipe, i, lds);
+      }
+    }
+    const int el = opaque_tid() & 63;
+    const int l31 = el & 31, hi = el >> 5;
+    const bool same_tile = c.ti == c.tj;
+    float rho = 0.f, rho1 = 0.f, zp = 0.f, zq = 0.f;
+#pragma unroll
+    for (int i = 0; i < G::NWAVES; ++i) {
+      const float4 f = red[i];
+      rho = fmaxf(rho, f.x);
+      rho1 = fmaxf(rho1, f.y);
+      if (i < G::NWAVES / 2) zp = fmaxf(zp, f.z);
+      else zq = fmaxf(zq, f.z);
+    }
+    const float band = (2.f * rho + rho * rho + 4e-3f) * 65536.f;
+    uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * 2 * kWavePairs;
+    float* ests = reinterpret_cast<float*>(pairs + kWavePairs);
+    // appends the pairs (this lane's row and column of a 32 x 32 block) with
+    // `hit` set: pairs of rows inside the bucket, on a diagonal tile each once
+    const int nra = c.n - c.ti * kTile, nrb = c.n - c.tj * kTile;
+    int np = 0;
+    auto push = [&](bool hit, float est, int row, int col) {
+      if (__ballot(hit) == 0) return;
+      hit = hit && row < nra && col < nrb && !(same_tile && row >= col);
+      const uint64_t m = __ballot(hit);
+      const int at = np + __popcll(m & lanemask_lt());
+      if (hit && at < kWavePairs) {
+        pairs[at] = static_cast<uint32_t>(row << 8 | col);
+        ests[at] = est;
+      }
+      np += __popcll(m);
+    };
+    auto any_over = [&](int limit) {   // block-uniform
+      if (el == 0) cnt[w] = np;
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      raw_barrier();
+      return __ballot(el < G::NWAVES && cnt[el & 7] > limit) != 0;
+    };
+    bool full = !two;          // block-uniform: the whole tile's products are taken
+    if (two) {
+      const float thr = (sa.h - (2.f * rho1 + rho1 * rho1 + 4e-3f) - zp * zq) * 65536.f;
+#pragma unroll
+      for (int fm = 0; fm < G::FM; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < G::FN; ++fn) {
+          constexpr int PER = (kDma + G::FM * G::FN - 1) / (G::FM * G::FN);
+          if (more) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+              if ((fm * G::FN + fn) * PER + i < kDma) G::issue_one(pipe, (fm * G::FN + fn) * PER + i, lds);
+          }
+          // most blocks have no pair left or one: maxima of four accumulators
+          // are tested before single ones
+          float m4[4];
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            m4[g] = fmaxf(fmaxf(acc[fm][fn][4 * g], acc[fm][fn][4 * g + 1]),
+                          fmaxf(acc[fm][fn][4 * g + 2], acc[fm][fn][4 * g + 3]));
+          if (__ballot(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])) >= thr) == 0) continue;
+          if (np > kWaveFirst) continue;   // too many already
+          const int row = wm * G::WTM + 32 * fm + 4 * hi, col = wn * G::WTN + 32 * fn + l31;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            if (__ballot(m4[g] >= thr) == 0) continue;
+#pragma unroll
+            for (int v = 4 * g; v < 4 * g + 4; ++v)
+              push(acc[fm][fn][v] >= thr, acc[fm][fn][v], row + 8 * (v >> 2) + (v & 3), col);
+          }
+        }
+      full = any_over(kWaveFirst);
+      if (full) {
+        // the rest of the values: the ring is taken back from the next tile
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        raw_barrier();
+        start(c, buf, KA, K - KA);
+        G::resume(pipe, lds, acc);
+        np = 0;
+      }
+    }
+    const bool first_only = !full;
+    if (full) {
+      // raw fp8 products of unit rows scaled by 2^8: c~ = acc / 2^16
+#pragma unroll
+      for (int fm = 0; fm < G::FM; ++fm) {
+        const int abase = wm * G::WTM + 32 * fm;
+        uint32_t col[G::FN];
+#pragma unroll
+        for (int fn = 0; fn < G::FN; ++fn) {
+          const int bbase = wn * G::WTN + 32 * fn;
+          // a token with itself is set to 0 (no edge for h > 0, and the word
+          // drops it below anyway)
           if (same_tile && abase == bbase) {
 #pragma unroll
             for (int v = 0; v < 16; ++v)
@@ -641,107 +987,203 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_kernel_bf16(
           // a 32 x 32 block without an edge (every product below 2^16 h,
           // the common case) needs only its largest product: no bits, and
           // its least distance to 2^16 h is 2^16 h minus that product
+          uint32_t bits = 0;
+          float dmin = __builtin_inff();
           float mx = acc[fm][fn][0];
 #pragma unroll
           for (int v = 1; v < 16; ++v) mx = fmaxf(mx, acc[fm][fn][v]);
           if (__ballot(mx >= hs) == 0) {
-            dmin = fminf(dmin, hs - mx);
+            dmin = hs - mx;
           } else {
 #pragma unroll
             for (int v = 15; v >= 0; --v) bits = shift_in_ge_band(bits, acc[fm][fn][v], hs, dmin);
           }
-        } else {
-          const float ib = inv_b[bl];
-          float p = acc[fm][fn][15] * ia[15] * ib;
+          if (__ballot(dmin < band) != 0 && np <= kWavePairs) {
 #pragma unroll
-          for (int v = 15; v >= 1; --v) {
-            float q;
-            bits = shift_in_ge_next(bits, p, h, acc[fm][fn][v - 1], ia[v - 1], ib, q);
-            p = q;
+            for (int v = 0; v < 16; ++v)
+              push(fabsf(acc[fm][fn][v] - hs) < band, 0.f, abase + 4 * hi + 8 * (v >> 2) + (v & 3), bbase + l31);
           }
-          bits = shift_in_ge_last(bits, p, h);
+          col[fn] = spread_col_bits(bits, hi, same_tile && abase == bbase, l31);
+          if (hi == 0) tbits[bbase + l31][abase >> 5] = col[fn];
         }
-        // nibble k (accumulators 4k..4k+3) to bits 8k..8k+3, then this half's rows
-        bits = (bits & 0xFFu) | ((bits & 0xFF00u) << 8);
-        bits = (bits & 0x000F000Fu) | ((bits & 0x00F000F0u) << 4);
-        bits <<= 4 * hi;
-        uint32_t cw = bits | static_cast<uint32_t>(__shfl_xor(static_cast<int>(bits), 32, 64));
-        if (same_tile && abase == bbase) cw &= ~(1u << l31);   // the token with itself
-        col[fn] = cw;
-        if (hi == 0) tbits[bl][abase >> 5] = cw;
+        store_row_bits(col[0], col[1], hi, l31, abase, wn * G::WTN, dbits);
       }
+      full = any_over(kWavePairs);   // from here on: too many pairs, hand the tile back
+      if (two && more) start(cn, buf ^ 1, 0, KA);
+    }
+    // the waves' lists taken as one, dealt to the waves a batch at a time
+    int pre[G::NWAVES + 1];   // scalars: pairs before each wave's
+    pre[0] = 0;
+    if (!full) {
+      const int mine = cnt[el & 7];
 #pragma unroll
-      for (int p = 0; p < G::FN / 2; ++p) {
-        // lower half-wave: block 2p, upper: block 2p + 1 (a select, not an
-        // indexed read, which would put col in memory)
-        const uint32_t sel = col[2 * p] ^ ((col[2 * p] ^ col[2 * p + 1]) & (0u - static_cast<uint32_t>(hi)));
-        const uint32_t rowbits = transpose32_bits(sel);
-        dbits[abase + l31][(wn * G::WTN + 32 * (2 * p + hi)) >> 5] = rowbits;
+      for (int i = 0; i < G::NWAVES; ++i) pre[i + 1] = pre[i] + __builtin_amdgcn_readlane(mine, i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < G::NWAVES; ++i) pre[i + 1] = 0;
+    }
+    const int all = pre[G::NWAVES];
+    const uint32_t* lists = reinterpret_cast<const uint32_t*>(lds + kListOff);
+    auto item = [&](int i) {   // place of pair i (< all) in the lists
+      int at = i;
+#pragma unroll
+      for (int q = 1; q < G::NWAVES; ++q)
+        if (i >= pre[q]) at = q * 2 * kWavePairs + i - pre[q];
+      return at;
+    };
+    uint32_t* close = reinterpret_cast<uint32_t*>(lds + kCloseOff) + w * kWavePairs;
+    int nclose = 0;
+    if (first_only) {
+      // the rest of the fp8 products, eight pairs at a time; a decided edge is
+      // set, the pairs still within the band are kept for the dot product
+      const int32_t* tk = tokens(buf);
+      constexpr int NP = 8;
+      for (int i0 = w * NP; i0 < all; i0 += G::NWAVES * NP) {
+        const uint8_t *pa[NP], *pb[NP];
+        float s[NP];
+        const int my = item(min(i0 + (el & (NP - 1)), all - 1));
+        const uint32_t pr = lists[my];
+        const int ta = tk[pr >> 8], tb = tk[kTile + (pr & 255)];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          pa[u] = sa.x8 + static_cast<size_t>(__builtin_amdgcn_readlane(ta, u)) * sa.dp;
+          pb[u] = sa.x8 + static_cast<size_t>(__builtin_amdgcn_readlane(tb, u)) * sa.dp;
+          s[u] = 0.f;
+        }
+        // two 1 KB pieces of every row in flight (the loads' latency, not their
+        // bytes, is what a batch waits for)
+        for (int cc = sa.da + el * 16; cc < sa.dp; cc += 2048) {
+          uint4 a[2][NP], b[2][NP];
+#pragma unroll
+          for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+              const bool in = cc + 1024 * h2 < sa.dp;
+              a[h2][u] = in ? *reinterpret_cast<const uint4*>(pa[u] + cc + 1024 * h2) : make_uint4(0u, 0u, 0u, 0u);
+              b[h2][u] = in ? *reinterpret_cast<const uint4*>(pb[u] + cc + 1024 * h2) : make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+          for (int h2 = 0; h2 < 2; ++h2)
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+              const uint32_t aw[4] = {a[h2][u].x, a[h2][u].y, a[h2][u].z, a[h2][u].w};
+              const uint32_t bw[4] = {b[h2][u].x, b[h2][u].y, b[h2][u].z, b[h2][u].w};
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const auto a0 = __builtin_amdgcn_cvt_pk_f32_fp8(aw[q], false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8(aw[q], true);
+                const auto b0 = __builtin_amdgcn_cvt_pk_f32_fp8(bw[q], false), b1 = __builtin_amdgcn_cvt_pk_f32_fp8(bw[q], true);
+                s[u] = fmaf(a0[0], b0[0], s[u]);
+                s[u] = fmaf(a0[1], b0[1], s[u]);
+                s[u] = fmaf(a1[0], b1[0], s[u]);
+                s[u] = fmaf(a1[1], b1[1], s[u]);
+              }
+            }
+        }
+        float rest = 0.f;   // of pair i0 + el % NP
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          const float t = wave_sum_dpp(s[u]);
+          rest = (el & (NP - 1)) == u ? t : rest;
+        }
+        const float d = reinterpret_cast<const float*>(lists)[my + kWavePairs] + rest - hs;
+        const bool mine = el < NP && i0 + el < all;
+        const bool near = mine && !(fabsf(d) >= band);   // (a NaN goes on to the dot product)
+        if (mine && d >= band) {
+          const int r = pr >> 8, q = pr & 255;
+          atomicOr(&dbits[r][q >> 5], 1u << (q & 31));
+          atomicOr(same_tile ? &dbits[q][r >> 5] : &tbits[q][r >> 5], 1u << (r & 31));
+        }
+        const uint64_t m = __ballot(near);
+        if (near) close[nclose + __popcll(m & lanemask_lt())] = pr;
+        nclose += __popcll(m);
       }
+      asm volatile("" ::: "memory");   // the kept entries cross lanes
     }
-    if constexpr (MODE == kGramScreen) {
-      if (__ballot(dmin < band) != 0 && el == 0) *flag = 1;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (nitem < total) {
+    if (first_only ? nclose > 0 : all > 0) {
+      // bf16 cosines, four pairs at a time; float32 sums of d products in any
+      // two orders differ by less than 2 d 2^-24 of |a| |b|
+      const float tie = static_cast<float>(2 * sa.d + 64) * 0x1p-24f;
+      const int32_t* tk = tokens(buf);
+      constexpr int NP = 4;
+      const int n4 = first_only ? nclose : all, step = first_only ? NP : G::NWAVES * NP;
+      for (int i0 = first_only ? 0 : w * NP; i0 < n4; i0 += step) {
+        const uint16_t *pa[NP], *pb[NP];
+        float s[NP];
+        const int my = min(i0 + (el & (NP - 1)), n4 - 1);
+        const uint32_t pr = first_only ? close[my] : lists[item(my)];
+        const int ta = tk[pr >> 8], tb = tk[kTile + (pr & 255)];
+        const float ia = sa.inv_norm[ta], ib = sa.inv_norm[tb];
 #pragma unroll
-      for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(ptok[j]) * d_units;
+        for (int u = 0; u < NP; ++u) {
+          pa[u] = sa.x + static_cast<size_t>(__builtin_amdgcn_readlane(ta, u)) * sa.d;
+          pb[u] = sa.x + static_cast<size_t>(__builtin_amdgcn_readlane(tb, u)) * sa.d;
+          s[u] = 0.f;
+        }
+        for (int cc = el * 8; cc < sa.d; cc += 512) {
+          Pack16 a[NP], b[NP];
 #pragma unroll
-      for (int j = 0; j < G::LQ; ++j) qoff[j] = static_cast<uint32_t>(qtok[j]) * d_units;
-      // before the DMA: waiting for them then does not wait for the DMA
+          for (int u = 0; u < NP; ++u) {
+            a[u].u4 = *reinterpret_cast<const uint4*>(pa[u] + cc);
+            b[u].u4 = *reinterpret_cast<const uint4*>(pb[u] + cc);
+          }
 #pragma unroll
-      for (int u = 0; u < NI; ++u) {
-        if constexpr (SCR) rh[u] = itok[u] >= 0 ? rho[itok[u]] : 0.f;
-        else inv[u] = gram_stage_inv(inv_norm, itok[u]);
-      }
-      G::prefetch(X, poff, X, qoff, d_units, SCR ? kTile : cn.n - cn.ti * kTile, SCR ? kTile : cn.n - cn.tj * kTile,
-                  lds, pipe);
-    }
-    // LDS-only barriers from here on: a full __syncthreads() would also wait
-    // for the next tile's DMA
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's pieces are in LDS
-    raw_barrier();
-    bool decided = true;
-    if constexpr (MODE == kGramScreen) {
-      decided = *flag == 0;
-      if (!decided && opaque_tid() == 0) list[atomicAdd(list_count, 1)] = tile;
-    }
-    if (decided) {
-      // degree: edges of each tile row (and, off the diagonal, of each mirrored row)
-      for (int i = opaque_tid(); i < 2 * kTile; i += G::THREADS) {
-        const bool mirror = i >= kTile;
-        const int rl = mirror ? i - kTile : i;
-        const uint32_t* pcs = mirror ? tbits[rl] : dbits[rl];
-        int cnt = 0;
+          for (int u = 0; u < NP; ++u)
 #pragma unroll
-        for (int g = 0; g < kTile / 32; ++g) cnt += __popc(pcs[g]);
-        const int r = (mirror ? c.tj : c.ti) * kTile + rl;
-        if (cnt && r < c.n && (!mirror || c.ti != c.tj)) atomicAdd(&deg[c.lo + r], cnt);
-      }
-      // write the words: 4 per row of the tile, direct and (off-diagonal) mirrored
-      for (int i = opaque_tid(); i < kTile * 4; i += G::THREADS) {
-        const int rl = i >> 2, ww = i & 3;
-        const uint64_t dv = static_cast<uint64_t>(dbits[rl][2 * ww]) |
-                            (static_cast<uint64_t>(dbits[rl][2 * ww + 1]) << 32);
-        const int a = c.ti * kTile + rl, wd = 4 * c.tj + ww;
-        if (a < c.n && wd < c.W) bitmask[bm_off[c.e] + static_cast<long long>(a) * c.W + wd] = dv;
-        if (c.ti != c.tj) {
-          const uint64_t tv = static_cast<uint64_t>(tbits[rl][2 * ww]) |
-                              (static_cast<uint64_t>(tbits[rl][2 * ww + 1]) << 32);
-          const int bb = c.tj * kTile + rl, wt = 4 * c.ti + ww;
-          if (bb < c.n && wt < c.W) bitmask[bm_off[c.e] + static_cast<long long>(bb) * c.W + wt] = tv;
+            for (int q = 0; q < 8; ++q) s[u] = fmaf(bf16_to_f32(a[u].h[q]), bf16_to_f32(b[u].h[q]), s[u]);
+        }
+        float dot = 0.f;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          const float t = wave_sum_dpp(s[u]);
+          dot = (el & (NP - 1)) == u ? t : dot;
+        }
+        const float cs = dot * ia * ib;
+        if (el < NP && i0 + el < n4) {
+          const int r = pr >> 8, q = pr & 255;
+          uint32_t* dw = &dbits[r][q >> 5];
+          uint32_t* tw = same_tile ? &dbits[q][r >> 5] : &tbits[q][r >> 5];
+          if (fabsf(cs - sa.h) < tie) cnt[8] = 1;
+          if (cs >= sa.h) {   // (a NaN cosine is no edge in either pass)
+            atomicOr(dw, 1u << (q & 31));
+            atomicOr(tw, 1u << (r & 31));
+          } else {
+            atomicAnd(dw, ~(1u << (q & 31)));
+            atomicAnd(tw, ~(1u << (r & 31)));
+          }
         }
       }
     }
-    if (nitem >= total) break;
-    // every wave's reads of the pieces, of inv_ab, rho_ab and the flag are
-    // done before the next tile overwrites them
+    // LDS-only barriers: a full __syncthreads() would also wait for the next
+    // tile's DMA
     __builtin_amdgcn_s_waitcnt(0xC07F);
     raw_barrier();
-    item = nitem;
-    tile = next;
+    if (!full && __builtin_amdgcn_readfirstlane(cnt[8]) == 0)
+      write_gram_tile(c, dbits, tbits, bitmask, bm_off[c.e], deg, G::THREADS);
+    else if (opaque_tid() == 0)
+      sa.list[atomicAdd(sa.list_count, 1)] = tile;
+    if (!more) break;
+    // every wave's reads of the tile's LDS state are done before the next
+    // tile overwrites it
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    raw_barrier();
+    tile = ntile;
     c = cn;
   }
+}
+
+// Values of a row the screen's first phase multiplies, a multiple of 128: the
+// fewest that leave unrelated pairs (cosine about 0, estimate spread
+// sqrt(f / d) over a share f of d values) well below h minus what the rows
+// keep beyond them (about 1 - f, spread with the rows) and the quantisation
+// bound (about 0.05 sqrt(f) + 0.004), or all of them (one phase) where that
+// would be more than half.  Only speed depends on it.
+int screen_first_values(int d, int dp, float h) {
+  for (int da = 128; 2 * da <= d; da += 128) {
+    const float f = static_cast<float>(da) / static_cast<float>(d);
+    const float room = h - (1.f - f), sd = sqrtf(f / static_cast<float>(d));
+    if (room >= 0.02f + 0.05f * sqrtf(f) + 6.f * sd) return da;
+  }
+  return dp;
 }
 
 // ------------------------------------------------------------ history
@@ -1775,10 +2217,10 @@ struct CondenseWs {
   int32_t* colinfo = nullptr;   // previous positions of every slot of every position
   int* queue = nullptr;         // tile queues of the similarity kernel
   // the fp8 screen (calls without history whose shape allows it): fp8 rows
-  // (and a zero row), their quantisation errors, the tiles left to the bf16
-  // pass and their count
+  // (and a zero row), their error bounds, the tiles left to the bf16 pass and
+  // their count
   uint8_t* x8 = nullptr;
-  float* rho = nullptr;
+  float4* rowq = nullptr;
   int* list = nullptr;
   int* list_count = nullptr;
 };
@@ -1786,13 +2228,17 @@ struct CondenseWs {
 // Process-wide switch of the fp8 similarity screen (on by default).
 std::atomic<int> g_gram_screen{1};
 
-// Shapes whose similarity call may take the fp8 screen: long products
-// (d >= 2048, whole 128-value fp8 stages) and buckets of MFMA-bound size
-// on average (T k / E >= 512); below that the extra pass over x costs
-// about what the screen saves.
+// Shapes whose similarity call may take the fp8 screen: long rows, and buckets
+// of MFMA-bound size on average (T k / E >= 512).  Below that the extra pass
+// over x and the looks at single pairs cost more than the products they save:
+// at d = 1024, 16 buckets of about 1100 tokens, bf16 products 34 us, screen 64
+// (its band, 0.067, covers same-group cosines of 0.999 against h = 0.95).
 bool gram_screen_shape(int T, int d, int E, int k) {
-  return d >= 2048 && d % 128 == 0 && static_cast<long long>(T) * k >= 512ll * E;
+  return d >= 2048 && static_cast<long long>(T) * k >= 512ll * E &&
+         static_cast<long long>(T + 1) * ((d + 127) / 128 * 128) <= 0xFFFF0000ll;
 }
+// Pitch of the fp8 rows: whole 128-value stages.
+int screen_pitch(int d) { return (d + 127) / 128 * 128; }
 
 // Upper bound of the number of similarity tiles: sum over buckets of
 // t_e (t_e + 1) / 2 with t_e = ceil(n_e / kTile) <= ceil(max_bucket / kTile)
@@ -1824,8 +2270,8 @@ CondenseWs carve_condense(Carver& c, int T, int d, int E, int k, int max_bucket,
     w.colinfo = c.take<int32_t>(static_cast<size_t>(S) * k);
     w.queue = c.take<int>(kTileQueues);
   } else if (gram_screen_shape(T, d, E, k)) {
-    w.x8 = c.take<uint8_t>(static_cast<size_t>(T + 1) * d);
-    w.rho = c.take<float>(T);
+    w.x8 = c.take<uint8_t>(static_cast<size_t>(T + 1) * screen_pitch(d));
+    w.rowq = c.take<float4>(T);
     w.list_count = c.take<int>(1);
     w.list = c.take<int>(static_cast<size_t>(gram_tile_bound(S, E, max_bucket)));
   }
@@ -1881,11 +2327,12 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
   const bool screen = !hc && bf16 && ws.x8 && threshold > 0.f && g_gram_screen.load(std::memory_order_relaxed);
   const int norm_blocks = screen ? std::max((S + 255) / 256, (T + 4) / 4)
                                  : inv_norm ? std::max(1, (S + 255) / 256) : (T + 3) / 4;
+  const int dp = screen_pitch(d), da = screen ? screen_first_values(d, dp, threshold) : 0;
   {
     const int tile = bf16 ? kTile : kTileF32;
 #define LUFFY_NORM_ARGS x, T, d, inv_norm ? const_cast<float*>(inv_norm) : ws.inv_norm, S, ws.deg, ws.state, ws.claim, \
                         offsets, E, max_bucket, tile, ws.cap_words, ws.tile_off, ws.bm_off, ws.err, stats, ws.queue,   \
-                        ws.left, ws.list_count, ws.x8, ws.rho
+                        ws.left, ws.list_count, dp, da, ws.x8, ws.rowq
     if (bf16 && screen) {
       if (inv_norm) launch("norm", norm_kernel<true, false, true>, norm_blocks, 256, 0, s, LUFFY_NORM_ARGS);
       else launch("norm", norm_kernel<true, true, true>, norm_blocks, 256, 0, s, LUFFY_NORM_ARGS);
@@ -1901,17 +2348,16 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
   if (!hc) {
     const uint16_t* xb = static_cast<const uint16_t*>(x);
     if (screen) {
-      // fp8 screen over every tile, then the bf16 pass over the tiles it left
-      launch("gram", gram_kernel_bf16<kGramScreen>, persistent_grid(), GramGemm::THREADS, 0, s,
-             reinterpret_cast<const uint16_t*>(ws.x8), d / 2, perm_token, offsets, E, nullptr, threshold,
-             ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg, ws.rho, ws.list, ws.list_count, T);
-      launch("gram_recheck", gram_kernel_bf16<kGramList>, persistent_grid(), GramGemm::THREADS, 0, s, xb, d,
-             perm_token, offsets, E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg,
-             nullptr, ws.list, ws.list_count, T);
+      // the screen over every tile, then the bf16 pass over the tiles it left
+      const ScreenArgs sa{ws.x8, ws.rowq, xb, inv_norm_use, d, dp, da, T, threshold, ws.list, ws.list_count};
+      launch("gram", gram_screen_kernel, persistent_grid(), GramGemm::THREADS, 0, s, sa, perm_token, offsets, E,
+             ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg);
+      launch("gram_recheck", gram_kernel_bf16<true>, persistent_grid(), GramGemm::THREADS, 0, s, xb, d, perm_token,
+             offsets, E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg, ws.list,
+             ws.list_count);
     } else if (bf16)
-      launch("gram", gram_kernel_bf16<kGramPlain>, persistent_grid(), GramGemm::THREADS, 0, s, xb, d, perm_token,
-             offsets, E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg, nullptr,
-             nullptr, nullptr, T);
+      launch("gram", gram_kernel_bf16<false>, persistent_grid(), GramGemm::THREADS, 0, s, xb, d, perm_token, offsets,
+             E, inv_norm_use, threshold, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg, nullptr, nullptr);
     else {
       HistParams hp{};
       hp.h = threshold;

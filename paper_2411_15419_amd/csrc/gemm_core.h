@@ -503,6 +503,30 @@ struct GemmCore {
       if (s < pro) issue(p.prs, p.qrs, p.goff, s, lds + s * STAGE_BYTES, w, pld, qld, kvalid, p.krow);
   }
 
+  // prefetch() in two halves for an epilogue that spreads the DMA over its
+  // own work: prepare() sets the tile up, issue_one() issues load i of the
+  // tile's first stages (0 <= i < STAGES * LOADS; row-major operands).
+  static __device__ __forceinline__ void prepare(const uint16_t* __restrict__ pbase, const uint32_t (&poff)[LP],
+                                                 const uint16_t* __restrict__ qbase, const uint32_t (&qoff)[LQ],
+                                                 int K, int pvalid, int qvalid, Pipe& p) {
+    static_assert(!PT && !QT, "row-major operands");
+    p.prs = rsrc(pbase);
+    p.qrs = rsrc(qbase);
+    p.pld = p.qld = 0;
+    p.kvalid = 0x7fffffff;
+    p.krow[0] = p.krow[1] = 0;
+    dma_offsets(poff, qoff, pvalid, qvalid, p.goff);
+    p.nk = __builtin_amdgcn_readfirstlane(K / BK);
+  }
+  static __device__ __forceinline__ void issue_one(const Pipe& p, int i, uint8_t* lds_generic) {
+    const int s = i / LOADS, j = i % LOADS;
+    if (s >= p.nk) return;   // wave-uniform
+    const lds_ptr dst = (lds_ptr)lds_generic + s * STAGE_BYTES + (wave() + NWAVES * j) * 1024;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(j < LP ? p.prs : p.qrs,
+                                             reinterpret_cast<__attribute__((address_space(3))) void*>(dst), 16,
+                                             p.goff[j], s * BK * 2, 0, 0);
+  }
+
   // poff[j] (j < LP): element offset of P row load_row(j);
   // qoff[j] (j < LQ): element offset of Q row load_row(LP + j) - BM.
   // Only the first pvalid P rows and qvalid Q rows are fetched; the LDS

@@ -1,0 +1,59 @@
+"""The similarity screen's two phases and its pair-by-pair decisions: a screened
+luffy_condense must give the outputs of the all-bf16 call bit for bit, whichever
+way a tile is decided (after the first values of the rows, after all of them,
+pair by pair on fp8 or bf16 rows, or handed back)."""
+import numpy as np
+import pytest
+
+import luffy_gen as G
+from tests.layer_runner import run_gpu, upload
+from tests.test_gpu_screen import _assert_same, _near_threshold_inputs, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2411_15419_amd as L
+    L.load_library()
+
+
+@pytest.mark.parametrize("T,E,k,d,h,n_centres", [
+    (3000, 4, 2, 2112, 0.9, 300),    # rows padded to 2176 values; ragged buckets
+    (2600, 2, 1, 2048, 0.9, 4),      # dense groups: every tile goes on to phase 2
+    (2600, 2, 1, 2048, 0.9, 60),     # about 30 to 40 pairs a wave: some tiles go on, some do not
+    (4096, 4, 2, 2048, 0.45, 512),   # a threshold whose first phase would be most of the row: one phase
+    (2048, 4, 2, 4096, 0.97, 256),
+    (2049, 4, 1, 8192, 0.9, 300),    # one row past a tile
+])
+def test_phases(T, E, k, d, h, n_centres):
+    inp = G.make_inputs("c3", seed=d + n_centres, weights=False, T=T, E=E, k=k, d=d, n_centres=n_centres)
+    inp.x[7] = 0.0                   # a zero row joins nothing
+    inp.x[11] *= 2.0 ** 40
+    inp.x[13] *= 2.0 ** -40
+    print(f"[case] T={T} E={E} k={k} d={d} h={h} centres={n_centres}", flush=True)
+    dev = upload(inp)
+    on = _run(inp, True, h=h, dev=dev)
+    off = _run(inp, False, h=h, dev=dev)
+    _assert_same(on, off)
+    assert on["degree"].max() > 0
+
+
+@pytest.mark.parametrize("near", [24, 200, 1200])
+def test_close_pairs_one_by_one(near):
+    """A few, some and many tokens whose cosines with each other cover the
+    threshold, among tight groups: pairs left within the band get their bf16
+    dot product, and tiles with too many of them are handed back."""
+    T, d, h = 2400, 2048, 0.9
+    inp = _near_threshold_inputs(T, d, h, 5)
+    rng = np.random.default_rng(near)
+    # keep `near` of the first half's tokens, the others i.i.d.
+    x = inp.x.copy()
+    x[near:T // 2] = rng.standard_normal((T // 2 - near, d)).astype(np.float32)
+    inp.x = G.round_bf16(x)[rng.permutation(T)]
+    print(f"[case] near={near}", flush=True)
+    dev = upload(inp)
+    _assert_same(_run(inp, True, h=h, dev=dev), _run(inp, False, h=h, dev=dev))
