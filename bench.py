@@ -219,7 +219,7 @@ def cpu_baseline(inp, h, full_bucket_sizes, budget_s=15.0):
                                               "other steps x T/T'"))
 
 
-BACKWARD_KERNELS = ("cbwd_group", "cbwd_rows", "cbwd_gate", "bwd_z", "bwd_act", "bwd_da", "bwd_dx",
+BACKWARD_KERNELS = ("cbwd_group", "cbwd_rows", "cbwd_gate", "bwd_z", "bwd_da", "bwd_dx",
                     "bwd_dx_reduce", "bwd_gather", "bwd_dw2", "bwd_dw1")
 
 

@@ -376,7 +376,7 @@ int luffy_adaptive_threshold(double l_ini, double l_prev, double* h_out);
  * hist_cols, hist_gather, hist_header, greedy_round, greedy_more,
  * greedy_finish, rep_local, rep_finalize, gather, ffn_queue, ffn1, ffn2,
  * ffn2_reduce, combine; backward: cbwd_group, cbwd_rows, cbwd_gate,
- * bwd_z, bwd_act, bwd_da, bwd_dx, bwd_dx_reduce, bwd_gather, bwd_dw2,
+ * bwd_z, bwd_da, bwd_dx, bwd_dx_reduce, bwd_gather, bwd_dw2,
  * bwd_dw1.
  * ---------------------------------------------------------------------- */
 int luffy_profile_kernel(const char* name);

@@ -96,6 +96,9 @@ __device__ __forceinline__ float act_grad(float z) {
 // Epilogue codes of the backward's dA product: multiply by act'(Z) read
 // from a second buffer (dZ = dA * act'(Z)).
 constexpr int kActDzGelu = 3, kActDzSilu = 4;
+// Epilogue codes of the backward's Z product: store Z to the output and
+// act(Z), taken on the rounded Z, to the second buffer.
+constexpr int kActZaGelu = 5, kActZaSilu = 6;
 
 // Tile shapes of the bf16 products: 256 output columns (weight rows, the P
 // operand) by up to 256 token rows (FfnGemm), or by up to 320 token rows
@@ -254,6 +257,26 @@ __device__ __forceinline__ void run_nq(int nq, const uint16_t* pbase, const uint
   }
 }
 
+// bf16 words pk[g] (columns 8g + 4 hi .. + 3 of a 32-column block of one token
+// row) of lanes l and l + 32: after one exchange the low lane stores columns
+// 0..15 and the high lane 16..31, two 16-byte stores each (dst: the lane's
+// first column).
+__device__ __forceinline__ void store_pair_row(const uint32_t (&pk)[4][2], int hi, uint16_t* __restrict__ dst_row) {
+  const uint32_t snd[4] = {hi ? pk[0][0] : pk[2][0], hi ? pk[0][1] : pk[2][1], hi ? pk[1][0] : pk[3][0],
+                           hi ? pk[1][1] : pk[3][1]};
+  uint32_t rcv[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) rcv[i] = static_cast<uint32_t>(__shfl_xor(static_cast<int>(snd[i]), 32, 64));
+  uint4* dst = reinterpret_cast<uint4*>(dst_row);
+  if (hi == 0) {
+    dst[0] = make_uint4(pk[0][0], pk[0][1], rcv[0], rcv[1]);
+    dst[1] = make_uint4(pk[1][0], pk[1][1], rcv[2], rcv[3]);
+  } else {
+    dst[0] = make_uint4(rcv[0], rcv[1], pk[2][0], pk[2][1]);
+    dst[1] = make_uint4(rcv[2], rcv[3], pk[3][0], pk[3][1]);
+  }
+}
+
 // One output tile (or one K part of it) of shape G: rows row0.. of A
 // (through row_index when given) times the weight rows n0.. of We over K
 // range [k0, k1).  Stores bf16 (activation applied when FIRST), or, when
@@ -263,8 +286,9 @@ template <class G, int ACT, bool FIRST>
 __device__ __forceinline__ void ffn_tile(const uint16_t* __restrict__ A, const int32_t* __restrict__ row_index,
                                          const uint16_t* __restrict__ We, int K, int N, int k0, int k1, int row0,
                                          int rows, int n0, uint16_t* __restrict__ out, float* __restrict__ slot,
-                                         const uint16_t* __restrict__ aux, uint8_t* lds) {
+                                         uint16_t* __restrict__ aux, uint8_t* lds) {
   static_assert(G::FN <= 5, "ragged dispatch instantiates FN + 1 main loops");
+  constexpr bool ZA = ACT == kActZaGelu || ACT == kActZaSilu;
   const int tid = opaque_tid(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = G::wave_m(w), wn = G::wave_n(w);
   uint32_t poff[G::LP], qoff[G::LQ];
@@ -287,10 +311,6 @@ __device__ __forceinline__ void ffn_tile(const uint16_t* __restrict__ A, const i
                    A + k0, qoff, k1 - k0, N - n0, rows, lds, acc, N);
   if constexpr (ACT != kActDzGelu && ACT != kActDzSilu) {
     if (!slot) {
-      // bf16 rows: lane l (< 32) holds columns 8g..8g+3 and lane l + 32
-      // columns 8g+4..8g+7 of a 32-column block of one token row; after one
-      // exchange the low lane stores columns 0..15 and the high lane 16..31,
-      // two 16-byte stores each
       const int hi = lane >> 5;
 #pragma unroll
       for (int fm = 0; fm < G::FM; ++fm) {
@@ -306,23 +326,22 @@ __device__ __forceinline__ void ffn_tile(const uint16_t* __restrict__ A, const i
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               z[q] = acc[fm][fn][4 * g + q];
-              if constexpr (FIRST) z[q] = act_fast<ACT>(z[q]);
+              if constexpr (FIRST && !ZA) z[q] = act_fast<ACT>(z[q]);
             }
             pk[g][0] = pack_bf16x2(z[0], z[1]);
             pk[g][1] = pack_bf16x2(z[2], z[3]);
           }
-          uint32_t snd[4] = {hi ? pk[0][0] : pk[2][0], hi ? pk[0][1] : pk[2][1], hi ? pk[1][0] : pk[3][0],
-                             hi ? pk[1][1] : pk[3][1]};
-          uint32_t rcv[4];
+          const size_t at = static_cast<size_t>(row0 + ml) * N + nb + 16 * hi;
+          store_pair_row(pk, hi, out + at);
+          if constexpr (ZA) {
+            constexpr int A = ACT == kActZaGelu ? LUFFY_ACT_GELU : LUFFY_ACT_SILU;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) rcv[i] = static_cast<uint32_t>(__shfl_xor(static_cast<int>(snd[i]), 32, 64));
-          uint4* dst = reinterpret_cast<uint4*>(out + static_cast<size_t>(row0 + ml) * N + nb + 16 * hi);
-          if (hi == 0) {
-            dst[0] = make_uint4(pk[0][0], pk[0][1], rcv[0], rcv[1]);
-            dst[1] = make_uint4(pk[1][0], pk[1][1], rcv[2], rcv[3]);
-          } else {
-            dst[0] = make_uint4(rcv[0], rcv[1], pk[2][0], pk[2][1]);
-            dst[1] = make_uint4(rcv[2], rcv[3], pk[3][0], pk[3][1]);
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+              for (int q = 0; q < 2; ++q)
+                pk[g][q] = pack_bf16x2(act_fast<A>(__uint_as_float(pk[g][q] << 16)),
+                                       act_fast<A>(__uint_as_float(pk[g][q] & 0xFFFF0000u)));
+            store_pair_row(pk, hi, aux + at);
           }
         }
       }
@@ -363,7 +382,7 @@ __device__ __forceinline__ void ffn_tile(const uint16_t* __restrict__ A, const i
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             z[q] = acc[fm][fn][4 * g + q];
-            if constexpr (FIRST) z[q] = act_fast<ACT>(z[q]);
+            if constexpr (FIRST && !ZA) z[q] = act_fast<ACT>(z[q]);
           }
         }
         *reinterpret_cast<uint2*>(orow + n) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
@@ -387,7 +406,7 @@ __global__ __launch_bounds__(FfnGemm::THREADS) void ffn_kernel_bf16(
     const uint16_t* __restrict__ A, const int32_t* __restrict__ row_index,
     const int32_t* __restrict__ rep_offsets, int E, int K, int N,
     const uint16_t* __restrict__ W, uint16_t* __restrict__ out, float* __restrict__ split_slots,
-    const uint16_t* __restrict__ aux, int* __restrict__ tail) {
+    uint16_t* __restrict__ aux, int* __restrict__ tail) {
   // one LDS array: the operand ring, then the block's current tail item (a
   // second LDS variable would cost the K loop its DMA overlap)
   __shared__ __attribute__((aligned(16))) uint8_t lds[kFfnLds + 16];
@@ -716,13 +735,13 @@ void launch_ffn(const void* x, const int32_t* row_index, const int32_t* rep_offs
     {
       launch("ffn1", ffn_kernel_bf16<ACT, true>, grid, FfnGemm::THREADS, 0, s, static_cast<const uint16_t*>(x),
              row_index, rep_offsets, E, d, d_ff, static_cast<const uint16_t*>(w1), static_cast<uint16_t*>(hidden),
-             ws.split_slots, static_cast<const uint16_t*>(nullptr), ws.queue);
+             ws.split_slots, static_cast<uint16_t*>(nullptr), ws.queue);
     }
     {
       launch("ffn2", ffn_kernel_bf16<ACT, false>, grid, FfnGemm::THREADS, 0, s,
              static_cast<const uint16_t*>(hidden), nullptr, rep_offsets, E, d_ff, d,
              static_cast<const uint16_t*>(w2), static_cast<uint16_t*>(y_rep), ws.split_slots,
-             static_cast<const uint16_t*>(nullptr), ws.queue + 1);
+             static_cast<uint16_t*>(nullptr), ws.queue + 1);
     }
     {
       launch("ffn2_reduce", ffn_split_reduce_kernel, 8 * grid, 256, 0, s, rep_offsets, E, d_ff, d, ws.split_slots,
@@ -746,24 +765,6 @@ void launch_ffn(const void* x, const int32_t* row_index, const int32_t* rep_offs
 // reads); the weight gradients contract over an expert's rows, read K-major
 // from the row-major activations, with the rows past the expert's read as
 // zeros up to the next multiple of 64.
-
-// A = act(Z) over the R = rep_offsets[E] rows of [*, d_ff] (8 per step).
-template <int ACT>
-__global__ __launch_bounds__(256) void act_rows_kernel(const int32_t* __restrict__ rep_offsets, int E, int d_ff,
-                                                       const uint16_t* __restrict__ z, uint16_t* __restrict__ a) {
-  const long long n8 = static_cast<long long>(rep_offsets[E]) * d_ff / 8;
-  const uint4* zz = reinterpret_cast<const uint4*>(z);
-  uint4* aa = reinterpret_cast<uint4*>(a);
-  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n8; i += static_cast<long long>(gridDim.x) * 256) {
-    const uint4 v = zz[i];
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      o[q] = pack_bf16x2(act_fast<ACT>(__uint_as_float(w[q] << 16)), act_fast<ACT>(__uint_as_float(w[q] & 0xFFFF0000u)));
-    aa[i] = make_uint4(o[0], o[1], o[2], o[3]);
-  }
-}
 
 // xg[r] = x[row_index[r]] for the R rows in use (one wave per row).
 __global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restrict__ rep_offsets, int E, int d,
@@ -894,19 +895,19 @@ void launch_ffn_bwd(const uint16_t* x, const int32_t* row_index, const int32_t* 
   const int grid = persistent_grid();
   const int egrid = 4 * grid;
   launch("ffn_queue", ffn_queue_clear_kernel, 1, 64, 0, s, ws.queue, 3);
-  // Z = X W1^T, A = act(Z)
-  launch("bwd_z", ffn_kernel_bf16<kActNone, true>, grid, FfnGemm::THREADS, 0, s, x, row_index, rep_offsets, E, d,
-         d_ff, w1, ws.z, ws.split_slots, static_cast<const uint16_t*>(nullptr), ws.queue);
-  launch("bwd_act", act_rows_kernel<ACT>, egrid, 256, 0, s, rep_offsets, E, d_ff, static_cast<const uint16_t*>(ws.z),
-         ws.a);
+  // Z = X W1^T and A = act(Z), both from the product's epilogue (a pass of its
+  // own that read Z back took 14 us for 4021 rows of 4096)
+  constexpr int kZa = ACT == LUFFY_ACT_GELU ? kActZaGelu : kActZaSilu;
+  launch("bwd_z", ffn_kernel_bf16<kZa, true>, grid, FfnGemm::THREADS, 0, s, x, row_index, rep_offsets, E, d, d_ff, w1,
+         ws.z, ws.split_slots, ws.a, ws.queue);
   // dZ = (dY W2) act'(Z): W2 [E][d][d_ff] read K-major (k = output row o)
   constexpr int kDz = ACT == LUFFY_ACT_GELU ? kActDzGelu : kActDzSilu;
   launch("bwd_da", ffn_kernel_bf16<kDz, true, true>, grid, FfnGemm::THREADS, 0, s, dy, nullptr, rep_offsets, E, d,
-         d_ff, w2, ws.dz, ws.split_slots, static_cast<const uint16_t*>(ws.z), ws.queue + 1);
+         d_ff, w2, ws.dz, ws.split_slots, ws.z, ws.queue + 1);
   // dX = dZ W1: W1 [E][d_ff][d] read K-major, split over K as the forward's second product
   launch("bwd_dx", ffn_kernel_bf16<kActNone, false, true>, grid, FfnGemm::THREADS, 0, s,
          static_cast<const uint16_t*>(ws.dz), nullptr, rep_offsets, E, d_ff, d, w1, dx, ws.split_slots,
-         static_cast<const uint16_t*>(nullptr), ws.queue + 2);
+         static_cast<uint16_t*>(nullptr), ws.queue + 2);
   launch("bwd_dx_reduce", ffn_split_reduce_kernel, 8 * grid, 256, 0, s, rep_offsets, E, d_ff, d, ws.split_slots, dx,
          grid);
   // dW2 = dY^T A, dW1 = dZ^T X (X's rows gathered first)
