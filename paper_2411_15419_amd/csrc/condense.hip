@@ -1390,6 +1390,164 @@ __global__ __launch_bounds__(256) void hist_gather_kernel(const int32_t* __restr
   }
 }
 
+// The same gather for buckets whose previous rows fit in LDS: the block's 8
+// rows' previous rows (both slots) are copied to LDS once, coalesced, hi and lo
+// words side by side, and a lane (column) then takes both class bits of its
+// previous position with one 8-byte LDS read.  The columns of a word keep their
+// order from block to block, so most of a wave's reads fall on two or three
+// words and are broadcasts.  A position is (previous bucket << 24) | place in it
+// (colinfo), so its exclusive or with a row's previous bucket << 24 is the place
+// itself where the buckets match and at least 2^24 where they do not; a token's
+// two slots lie in different buckets, so at most one matches.  Neighbouring rows
+// mostly come from the same previous bucket (a bucket holds its first choices,
+// then its second ones), and the columns' places in it are then taken over from
+// the row before.  The kernel is bound by its vector instructions, 8 to 25 per
+// row and 64 columns (with a row's words in memory and 64-bit addresses about
+// 60, and one-lane stores), and by a block's chain of loads before it starts,
+// which the other block of the CU hides.  65536 slots in 32 buckets of up to
+// 19,400: 1005 -> 360 us (one block a CU 423, its rows copied one after the
+// other 620); 16384 in 16 of at most 1280: 53 -> 25 us.
+constexpr uint32_t kNoBucket = 0xC0000000u;   // matches no position
+constexpr size_t kGatherLdsMax = 76 * 1024;   // two blocks in a CU's 160 KB
+
+// Bytes of one previous row in LDS: 8 bytes per 32 positions and a zero entry
+// (the last) for columns that were not in its bucket.
+inline size_t hist_row_bytes(int max_bucket) { return (static_cast<size_t>(max_bucket) + 63) / 64 * 16 + 16; }
+
+template <int K, int G>
+__global__ __launch_bounds__(1024) void hist_gather_lds_kernel(const int32_t* __restrict__ offsets, int E,
+                                                              const long long* __restrict__ bm_off,
+                                                              const int* __restrict__ err, HistRec in, int row_bytes,
+                                                              const int32_t* __restrict__ colinfo,
+                                                              uint64_t* __restrict__ rb_hi,
+                                                              uint64_t* __restrict__ rb_lo) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t rows_lds[];   // [row][slot][row_bytes]
+  if (*err) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // this block's bucket and first row: lane e holds bucket e's row groups
+  const int o0 = lane < E ? offsets[lane] : 0;
+  const int nl = lane < E ? offsets[lane + 1] - o0 : 0;
+  const int g = (nl + G - 1) / G;
+  int incl = g;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  const int b = blockIdx.x;
+  const int e = __popcll(__ballot(lane < E && incl <= b));
+  if (e >= E) return;
+  const int lo = __builtin_amdgcn_readlane(o0, e), n = __builtin_amdgcn_readlane(nl, e), W = (n + 63) / 64;
+  const int a0 = (b - (__builtin_amdgcn_readlane(incl, e) - __builtin_amdgcn_readlane(g, e))) * G;
+  const int rows = min(G, n - a0);
+  // previous bucket and first word of every row and slot (lane i K + j)
+  int ri = -1, pw = 0;
+  long long base = 0;
+  if (lane < rows * K) {
+    ri = colinfo[static_cast<size_t>(lo + a0) * K + lane];
+    if (ri >= 0) {
+      const int pe = ri >> 24;
+      pw = (in.offsets[pe + 1] - in.offsets[pe] + 63) / 64;
+      base = in.word_off[pe] + static_cast<long long>(ri & 0xFFFFFF) * pw;
+    }
+  }
+  // entry 2 w (2 w + 1): low (high) half of word w of both classes, bit-reversed
+  // so that a left shift by a place brings its bit to the sign
+  const int zero_idx = row_bytes / 8 - 1;
+  for (int r = w; r < G * K; r += static_cast<int>(blockDim.x) / 64) {   // a wave a row
+    const int words = __builtin_amdgcn_readlane(pw, r);
+    const long long at = (static_cast<long long>(__builtin_amdgcn_readlane(static_cast<int>(base >> 32), r)) << 32) |
+                         static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(base), r));
+    uint8_t* row = rows_lds + static_cast<size_t>(r) * row_bytes;
+    constexpr int U = 4;   // pieces of the row in flight
+    for (int i0 = lane; i0 < words; i0 += 64 * U) {
+      uint64_t h[U], l[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool in_row = i0 + 64 * u < words;
+        h[u] = in_row ? in.hi[at + i0 + 64 * u] : 0ull;
+        l[u] = in_row ? in.lo[at + i0 + 64 * u] : 0ull;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + 64 * u < words)
+          *reinterpret_cast<uint4*>(row + 16 * (i0 + 64 * u)) =
+              make_uint4(__brev(static_cast<uint32_t>(h[u])), __brev(static_cast<uint32_t>(l[u])),
+                         __brev(static_cast<uint32_t>(h[u] >> 32)), __brev(static_cast<uint32_t>(l[u] >> 32)));
+    }
+    if (lane == 0) *reinterpret_cast<uint2*>(row + 8 * zero_idx) = make_uint2(0u, 0u);
+  }
+  uint32_t P[G][K];   // scalars
+#pragma unroll
+  for (int i = 0; i < G; ++i)
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const int v = __builtin_amdgcn_readlane(ri, i * K + j);
+      P[i][j] = v >= 0 ? static_cast<uint32_t>(v) & 0xFF000000u : kNoBucket;
+    }
+  __syncthreads();
+  // the lane that stores: row lane % 8 of class hi (lanes 0-7) or lo (8-15)
+  const bool store = lane < 2 * G && (lane & (G - 1)) < rows;
+  uint64_t* dst = (lane < G ? rb_hi : rb_lo) + bm_off[e] + static_cast<long long>(a0 + (lane & (G - 1))) * W;
+  // two words (128 columns) a wave and pass: 16 bytes a storing lane
+  for (int wd = 2 * w; wd < W; wd += blockDim.x / 32) {
+    int ww[2][2] = {};   // [word][half]: lane i: row i's hi word; lane 8 + i: its lo word
+#pragma unroll
+    for (int h2 = 0; h2 < 2; ++h2) {
+      const int c = (wd + h2) * 64 + lane;
+      uint32_t qv[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) qv[j] = c < n ? static_cast<uint32_t>(colinfo[static_cast<size_t>(lo + c) * K + j]) : ~0u;
+      // the columns' places in the row's previous bucket (slot j), kept while
+      // the bucket stays the same from row to row; offset of their entry
+      uint32_t m[K], at[K];
+      bool miss = false;   // a column was not in the first slot's bucket (wave-uniform)
+      auto places = [&](uint32_t bucket, int j) {
+        uint32_t x = qv[0] ^ bucket;
+        if constexpr (K == 2) x = min(x, qv[1] ^ bucket);
+        m[j] = x;
+        at[j] = 8u * min(x >> 5, static_cast<uint32_t>(zero_idx));
+      };
+      uint2 v[G];
+      uint32_t pos[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        if (i == 0 || P[i][0] != P[i - 1][0]) {
+          places(P[i][0], 0);
+          miss = __ballot(m[0] >= (1u << 24)) != 0;
+        }
+        const uint8_t* row = rows_lds + static_cast<uint32_t>(i * K) * row_bytes;
+        uint32_t off = at[0];
+        pos[i] = m[0];
+        if constexpr (K == 2) {
+          // the row's first slot takes precedence over its second
+          if (miss) {
+            places(P[i][1], 1);
+            const bool second = m[0] >= (1u << 24);
+            off = second ? at[1] + row_bytes : off;
+            pos[i] = second ? m[1] : m[0];
+          }
+        }
+        v[i] = *reinterpret_cast<const uint2*>(row + off);
+      }
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        const uint64_t mh = __ballot(static_cast<int>(v[i].x << (pos[i] & 31)) < 0);
+        const uint64_t ml = __ballot(static_cast<int>(v[i].y << (pos[i] & 31)) < 0);
+        ww[h2][0] = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(mh)), i, ww[h2][0]);
+        ww[h2][1] = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(mh >> 32)), i, ww[h2][1]);
+        ww[h2][0] = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(ml)), G + i, ww[h2][0]);
+        ww[h2][1] = amdgcn_writelane(static_cast<int>(static_cast<uint32_t>(ml >> 32)), G + i, ww[h2][1]);
+      }
+    }
+    if (store) {
+      const uint4 o = make_uint4(ww[0][0], ww[0][1], ww[1][0], ww[1][1]);
+      if (wd + 1 < W) __builtin_memcpy(dst + wd, &o, 16);
+      else __builtin_memcpy(dst + wd, &o, 8);
+    }
+  }
+}
+
 // Constants of a block's pair weights: a decided pair's weight is 1 or 0,
 // which gives its edge (w >= h) and its classes for the next block
 // (w > S1, w < S2) without a cosine.
@@ -2372,14 +2530,32 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
     if (hc->in) {
       const int blocks = (S + kGatherRows - 1) / kGatherRows + E;
       const int cblocks = std::max(1, std::min(1024, (S + 255) / 256));
-      if (k == 1) {
+      // the rows in LDS where they fit a CU: 8 rows a block by four waves while
+      // four blocks fit, 8 by 16 waves while two do, else 4 by 16 waves (buckets
+      // of up to 36,000 tokens at k = 2 then still give a CU two blocks, whose
+      // row copies and lookups overlap); larger buckets read the rows from memory
+      const size_t row_lds = hist_row_bytes(max_bucket);
+      const int row_bytes = static_cast<int>(row_lds);
+      const bool eight = 8 * k * row_lds <= kGatherLdsMax;
+      const int grows = eight ? 8 : 4, gthreads = eight && 8 * k * row_lds <= kGatherLdsMax / 2 ? 256 : 1024;
+      const size_t glds = grows * k * row_lds;
+      const int gblocks = (S + grows - 1) / grows + E;
+#define LUFFY_GATHER(K_, G_) launch("hist_gather", hist_gather_lds_kernel<K_, G_>, gblocks, gthreads, glds, s, offsets, E, \
+                                    ws.bm_off, ws.err, rin, row_bytes, ws.colinfo, ws.rb_hi, ws.rb_lo)
+      if (k == 1)
         launch("hist_cols", hist_cols_kernel<1>, cblocks, 256, 0, s, offsets, E, perm_token, ws.err, rin, T,
                max_bucket, ws.colinfo);
+      else
+        launch("hist_cols", hist_cols_kernel<2>, cblocks, 256, 0, s, offsets, E, perm_token, ws.err, rin, T,
+               max_bucket, ws.colinfo);
+      if (glds <= kGatherLdsMax) {
+        if (k == 1) { if (eight) LUFFY_GATHER(1, 8); else LUFFY_GATHER(1, 4); }
+        else { if (eight) LUFFY_GATHER(2, 8); else LUFFY_GATHER(2, 4); }
+#undef LUFFY_GATHER
+      } else if (k == 1) {
         launch("hist_gather", hist_gather_kernel<1>, blocks, 256, 0, s, offsets, E, ws.bm_off, ws.err, rin,
                ws.colinfo, ws.rb_hi, ws.rb_lo);
       } else {
-        launch("hist_cols", hist_cols_kernel<2>, cblocks, 256, 0, s, offsets, E, perm_token, ws.err, rin, T,
-               max_bucket, ws.colinfo);
         launch("hist_gather", hist_gather_kernel<2>, blocks, 256, 0, s, offsets, E, ws.bm_off, ws.err, rin,
                ws.colinfo, ws.rb_hi, ws.rb_lo);
       }
