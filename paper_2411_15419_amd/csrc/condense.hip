@@ -2110,19 +2110,21 @@ __global__ __launch_bounds__(256) void greedy_more_kernel(
     const int pq = base + gl;
     const bool und = pq < S && load_flag(&state[pq]) == kStateUndecided;
     uint32_t m = static_cast<uint32_t>((__ballot(und) >> gshift) & ((1ull << kVisitLanes) - 1));
-    while (m) {
-      const int p = base + __ffs(m) - 1;
-      m &= m - 1;
-      const int e = bucket_of(soff, E, p);
-      const int lo = soff[e], n = soff[e + 1] - lo, W = (n + 63) / 64;
-      const uint64_t* row = bitmask + bm_off[e] + static_cast<long long>(p - lo) * W;
-      bool still = greedy_visit<true, kVisitLanes>(p, lo, n, W, row, deg, state, claim);
-      for (int pass = 1; still && pass < kGreedyPasses; ++pass) {
-        __builtin_amdgcn_s_sleep(32);
-        still = greedy_visit<true, kVisitLanes>(p, lo, n, W, row, deg, state, claim);
+    // every pass visits each position the group still has: one of them may wait
+    // for another (visited to the end one after the other, such a position spent
+    // all its passes first: 8192 tokens with one mixture of two groups in twenty,
+    // threshold 0.45: 70 us, now 12)
+    for (int pass = 0; m && pass < kGreedyPasses; ++pass) {
+      if (pass > 0) __builtin_amdgcn_s_sleep(32);
+      for (uint32_t todo = m; todo; todo &= todo - 1) {
+        const int p = base + __ffs(todo) - 1;
+        const int e = bucket_of(soff, E, p);
+        const int lo = soff[e], n = soff[e + 1] - lo, W = (n + 63) / 64;
+        const uint64_t* row = bitmask + bm_off[e] + static_cast<long long>(p - lo) * W;
+        if (!greedy_visit<true, kVisitLanes>(p, lo, n, W, row, deg, state, claim)) m &= ~(todo & (0u - todo));
       }
-      if (still && gl == 0) store_flag(&left[0], 1);
     }
+    if (m && gl == 0) store_flag(&left[0], 1);
   }
 }
 
