@@ -180,8 +180,9 @@ int luffy_condense(const void* x, int T, int d, int dtype,
                    void* workspace, size_t workspace_bytes, void* stream);
 
 /* ------------------------------------------------------------------------
- * Similarity screen of luffy_condense (bf16 calls with d >= 2048 and
- * T*k >= 512*E; not luffy_condense_history).  The
+ * Similarity screen of luffy_condense and luffy_condense_history (bf16 calls
+ * with d >= 2048, T*k >= 512*E and threshold > 0; of luffy_condense_history
+ * those that leave a record).  The
  * cosines of Sec. 5.1 are first estimated on fp8 (E4M3) copies of the rows,
  * each normalised, with a bound derived from every row's
  * quantisation error: |c~ - c| <= rho_a + rho_b + rho_a*rho_b (plus room for
@@ -191,6 +192,8 @@ int luffy_condense(const void* x, int T, int d, int dtype,
  * agrees with the exact comparison; a tile's few other pairs are decided by
  * their own dot products, and a 256 x 256 tile with many of them, or with one
  * within float32 rounding of the threshold, is recomputed from the bf16 rows.
+ * With history the three comparisons of a pair (>= h, > S1, < S2) are decided
+ * in the same way.
  * The outputs are the same with the screen on or off.  The workspace of such
  * calls holds the fp8 rows (T+1 rows of d rounded up to 128 bytes).
  *

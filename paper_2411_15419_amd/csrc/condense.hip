@@ -13,6 +13,9 @@
 //                        bits, writes both the tile and its transpose (every
 //                        bitmask word is written exactly once) and adds each
 //                        row's edge count to its degree.
+//   gram_hist_screen_kernel, gram_hist_kernel_bf16  the same two with the
+//                        previous block's record of pair classes: decided pairs
+//                        keep their class, the others' classes are recorded.
 //   greedy_round_kernel  first round of the parallel form of the greedy
 //                        walk, 16 lanes per position: keeps every position
 //                        with no undecided neighbour of higher priority.
@@ -29,6 +32,7 @@
 //                        when the pass before left a position undecided).
 //   rep_local_kernel, rep_finalize_kernel  representative rows by a two-pass
 //                        scan: rep_row, rep_token, rep_offsets.
+//   greedy_small_kernel  (at most 4096 slots) the last four in one launch.
 //   gather_kernel        optional copy of the representative rows.
 //
 // The walk of Sec. 5.2 visits positions by priority (degree descending,
@@ -134,6 +138,23 @@ __device__ __forceinline__ void gram_quant_row(const uint16_t* __restrict__ x, i
     return;
   }
   const uint16_t* row = x + static_cast<size_t>(t) * d;
+  if (inv == 0.f) {
+    // a finite row whose squares over- or underflow: its cosines are 0 or NaN as
+    // the bf16 products fall out, so no bound holds and its tiles are handed back
+    uint32_t m = 0;
+    for (int c = lane * 8; c < d; c += 512) {
+      Pack16 v;
+      v.u4 = *reinterpret_cast<const uint4*>(row + c);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m = max(m, static_cast<uint32_t>(v.h[i] & 0x7FFF));
+    }
+    if (__ballot(m >= 0x7F80u) == 0 && __ballot(m != 0) != 0) {
+      for (int c = lane * 8; c < dp; c += 512) *reinterpret_cast<uint2*>(out + c) = make_uint2(0u, 0u);
+      const float big = __builtin_inff();
+      if (lane == 0) rowq[t] = make_float4(big, big, big, 0.f);
+      return;
+    }
+  }
   const float sc = inv * 256.f;
   float se = 0.f, sx = 0.f, sea = 0.f, sxb = 0.f;   // error and square sums; error of the first da, squares of the rest
   for (int c = lane * 8; c < dp; c += 512) {
@@ -1590,12 +1611,15 @@ __device__ __forceinline__ uint64_t pair_mask(int row, int wd, int n) {
 // or 0 where the previous block decided it and the cosine elsewhere.  The
 // record of this block (classes of every weight) is written beside the
 // adjacency words, direct and mirrored.
-template <bool HIN, bool HOUT>
+// LIST: only the tiles the history screen handed back (which has counted their
+// pairs).
+template <bool HIN, bool HOUT, bool LIST = false>
 __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
     const uint16_t* __restrict__ X, int d, const int32_t* __restrict__ perm_token,
     const int32_t* __restrict__ offsets, int E, const float* __restrict__ inv_norm, HistParams hp,
     const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off,
-    const int* __restrict__ err, uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg) {
+    const int* __restrict__ err, uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg,
+    const int* __restrict__ list, const int* __restrict__ list_count) {
   using G = GramGemm;
   __shared__ __attribute__((aligned(16))) uint8_t lds[G::LDS_BYTES];
   __shared__ __attribute__((aligned(16))) float inv_a[kTile];
@@ -1611,7 +1635,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
   if (*err) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = G::wave_m(w), wn = G::wave_n(w);
-  const int total = tile_off[E];
+  const int total = LIST ? *list_count : tile_off[E];
   // Tiles cost very different times (skipped or computed), so blocks take
   // them from queues: queue x holds the x-th eighth of the tile order, a
   // block first drains the queue of its own XCD (blocks are dealt to the
@@ -1636,8 +1660,8 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
       next_tile = t;
     }
     __syncthreads();
-    const int tile = next_tile;
-    if (tile < 0) break;
+    if (next_tile < 0) break;
+    const int tile = LIST ? list[next_tile] : next_tile;
     const TileCoord c = decode_tile_grouped(tile, tile_off, offsets, E);
     const int32_t* pt = perm_token + c.lo;
     const long long bmo = bm_off[c.e];
@@ -1678,7 +1702,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
       if (nd) atomicAdd(&cnt_s[1], nd);
     }
     undecided = __syncthreads_or(undecided);
-    if (tid == 0) {
+    if (!LIST && tid == 0) {
       atomicAdd(&hp.stats[0], cnt_s[0]);
       atomicAdd(&hp.stats[1], cnt_s[1]);
       atomicAdd(&hp.stats[undecided ? 2 : 3], 1ull);
@@ -1815,6 +1839,382 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
       }
     }
     __syncthreads();
+  }
+}
+
+// Words wd and wd + 1 of bitmask row `row` for the pairs of a tile: previous
+// classes (if any) decide a pair's weight, its cosine's predicates e, g, l (weight
+// >= h, > S1, < S2; bit pieces of 64 columns) the others.  Returns the row's
+// edges among them.
+__device__ __forceinline__ int store_hist_words(const HistParams& hp, uint64_t* __restrict__ bitmask, long long base,
+                                                int row, int wd, int n, int W, const uint32_t* e, const uint32_t* g,
+                                                const uint32_t* l) {
+  if (row >= n || wd >= W) return 0;
+  const long long o = base + static_cast<long long>(row) * W + wd;
+  const int nw = min(2, W - wd);
+  uint64_t oe[2], oh[2], ol[2];
+  int edges = 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const uint64_t vm = u < nw ? pair_mask(row, wd + u, n) : 0ull;
+    uint64_t one = 0, zero = 0;
+    if (hp.rb_hi && u < nw) {
+      one = hp.rb_hi[o + u];
+      zero = hp.rb_lo[o + u];
+    }
+    decided_words(one, zero, vm, hp, oe[u], oh[u], ol[u]);
+    const uint64_t und = ~(one | zero) & vm;
+    auto word = [&](const uint32_t* p) { return static_cast<uint64_t>(p[2 * u]) | (static_cast<uint64_t>(p[2 * u + 1]) << 32); };
+    oe[u] |= und & word(e);
+    oh[u] |= und & word(g);
+    ol[u] |= und & word(l);
+    edges += __popcll(oe[u]);
+  }
+  if (nw == 2) {
+    __builtin_memcpy(bitmask + o, oe, 16);
+    __builtin_memcpy(hp.out_hi + o, oh, 16);
+    __builtin_memcpy(hp.out_lo + o, ol, 16);
+  } else {
+    bitmask[o] = oe[0];
+    hp.out_hi[o] = oh[0];
+    hp.out_lo[o] = ol[0];
+  }
+  return edges;
+}
+
+// History similarity on the fp8 screen's rows (see gram_screen_kernel): a tile
+// with an undecided pair takes its whole fp8 product, whose band decides a
+// pair's three predicates (>= h, > S1, < S2) where its estimate is further than
+// the band from all three thresholds; the few pairs closer to one get their
+// bf16 dot product, and a tile with more than kWavePairs of them in a wave, or
+// a dot product within float32 rounding of a threshold, is listed for the bf16
+// pass.  The predicates' bit pieces of a tile are merged with its previous
+// classes word by word as they are stored; most 32 x 32 blocks lie below every
+// threshold as a whole and need no compares.  A tile whose pairs are all
+// decided skips the product.  The tile loop is pipelined as the screen's, with
+// one stage of the next tile's operands in flight: the other stage's LDS holds
+// the pieces.
+// Why: the bf16 kernel spent 77,000 cycles of a 256 x 256 tile of d = 2048 on
+// its K loop and as many on 3 predicates with two bit lookups a pair; fp8 halves
+// the first and the word-level merge leaves one compare a predicate.  Two
+// blocks of T = 32768, d = 2048, E = 32 (Zipf): 1390 -> 640 us a block, of which
+// 28 in the bf16 pass over what is handed back and 32 in the fp8 rows.
+__global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
+    ScreenArgs sa, HistParams hp, const int32_t* __restrict__ perm_token, const int32_t* __restrict__ offsets, int E,
+    const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off, const int* __restrict__ err,
+    uint64_t* __restrict__ bitmask, int32_t* __restrict__ deg) {
+  using G = GemmBig64F8;
+  constexpr int kPieces = kTile * (kTile / 32) * 4;   // bytes of one mask's pieces, direct or transposed
+  static_assert(G::STAGES == 2 && 6 * kPieces <= G::STAGE_BYTES && G::THREADS == 2 * kTile && G::NWAVES == 8,
+                "three masks' pieces in the second stage");
+  // one LDS array (see gram_kernel_bf16): the operand ring, whose second stage
+  // holds the pieces d[m], then t[m], between K loops; the waves' row bounds,
+  // the tokens of this tile and of the next, the bucket tables, every wave's
+  // close pairs, their counts and the flags
+  constexpr int kRedOff = G::LDS_BYTES, kTokOff = kRedOff + G::NWAVES * 4 + 32, kTabOff = kTokOff + 4 * kTile * 4;
+  constexpr int kListOff = kTabOff + 3 * kMaxExperts * 4, kCntOff = kListOff + G::NWAVES * kWavePairs * 4;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kCntOff + 48];
+  float* red = reinterpret_cast<float*>(lds + kRedOff);
+  auto pieces = [&](int m, bool t) {
+    return reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + G::STAGE_BYTES + (m + (t ? 3 : 0)) * kPieces);
+  };
+  int* tab = reinterpret_cast<int*>(lds + kTabOff);
+  int* cnt = reinterpret_cast<int*>(lds + kCntOff);   // [w]: pairs of wave w; [8]: hand back; [9]: undecided pairs
+  if (*err) return;
+  const int w = G::wave();
+  const int wm = G::wave_m(w), wn = G::wave_n(w);
+  const int total = tile_off[E];
+  int tile = xcd_virtual_block();
+  if (tile >= total) return;   // block-uniform, before any barrier
+  const uint16_t* X = reinterpret_cast<const uint16_t*>(sa.x8);
+  const int K = sa.dp / 2;   // 16-bit units, 64 a stage
+  if (w == 0) {
+    int to, o0, o1;
+    bucket_lookup_loads(tile_off, offsets, E, to, o0, o1);
+    const int l = opaque_tid();
+    tab[l] = to;
+    tab[kMaxExperts + l] = o0;
+    tab[2 * kMaxExperts + l] = o1;
+  }
+  __syncthreads();
+  auto decode = [&](int t) {
+    const int l = opaque_tid() & 63;
+    return decode_tile_grouped_from(t, tab[l], tab[kMaxExperts + l], tab[2 * kMaxExperts + l], E);
+  };
+  auto tokens = [&](int buf) { return reinterpret_cast<int32_t*>(lds + kTokOff) + buf * 2 * kTile; };
+  auto fetch_tokens = [&](const TileCoord& t, int buf) {
+    const int l = opaque_tid() & 63;
+    const int r = (w < 4 ? t.ti : t.tj) * kTile + 64 * (w & 3) + l;
+    const uint32_t off = static_cast<uint32_t>(t.lo + min(r, t.n - 1)) * 4u;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        G::rsrc(perm_token),
+        reinterpret_cast<__attribute__((address_space(3))) void*>((G::lds_ptr)(lds + kTokOff) + (buf * 2 * kTile + 64 * w) * 4),
+        4, off, 0, 0, 0);
+  };
+  typename G::Pipe pipe;
+  auto prepare = [&](const TileCoord& t, int buf) {
+    const int32_t* tk = tokens(buf);
+    uint32_t poff[G::LP], qoff[G::LQ];
+#pragma unroll
+    for (int j = 0; j < G::LP; ++j) {
+      const int r = G::load_row(j);
+      poff[j] = static_cast<uint32_t>(t.ti * kTile + r < t.n ? tk[r] : sa.T) * K;
+    }
+#pragma unroll
+    for (int j = 0; j < G::LQ; ++j) {
+      const int r = G::load_row(G::LP + j) - G::BM;
+      qoff[j] = static_cast<uint32_t>(t.tj * kTile + r < t.n ? tk[kTile + r] : sa.T) * K;
+    }
+    G::prepare(X, poff, X, qoff, K, kTile, kTile, pipe);
+  };
+  auto issue_stage = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < G::LOADS; ++i) G::issue_one(pipe, st * G::LOADS + i, lds);
+  };
+  auto bound = [&](const TileCoord& t, int buf) {
+    const int i = opaque_tid();
+    const int r = (i < kTile ? t.ti : t.tj - 1) * kTile + i;
+    return r < t.n ? sa.rowq[tokens(buf)[i]].x : 0.f;
+  };
+  TileCoord c = decode(tile);
+  fetch_tokens(c, 0);
+  __syncthreads();   // (waits for the DMA too)
+  float rq = bound(c, 0);
+  prepare(c, 0);
+  issue_stage(0);
+  const float te = sa.h * 65536.f, tg = hp.S1 * 65536.f, tl = hp.S2 * 65536.f;
+  const float tmin = fminf(fminf(te, tg), tl);
+  unsigned long long nu = 0, nd = 0, tiles = 0, skipped = 0;
+  for (int buf = 0;; buf ^= 1) {
+    const int ntile = tile + gridDim.x;
+    const bool more = ntile < total;
+    const long long base = bm_off[c.e];
+    const bool same_tile = c.ti == c.tj;
+    issue_stage(1);
+    TileCoord cn = c;
+    if (more) {
+      cn = decode(ntile);
+      fetch_tokens(cn, buf ^ 1);   // lands under the K loop
+    }
+    // the tile's undecided and decided pairs above the diagonal
+    int undecided = 0;
+    {
+      const int i = opaque_tid(), rl = i >> 1;
+      const int a = c.ti * kTile + rl;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int wd = 4 * c.tj + 2 * (i & 1) + u;
+        if (a < c.n && wd < c.W) {
+          const uint64_t vm = pair_mask(a, wd, c.n);
+          uint64_t dec = 0;
+          if (hp.rb_hi) {
+            const long long o = base + static_cast<long long>(a) * c.W + wd;
+            dec = hp.rb_hi[o] | hp.rb_lo[o];
+          }
+          const uint64_t und = ~dec & vm;
+          undecided |= und != 0;
+          uint64_t up = ~0ull;
+          if (same_tile) {
+            const int c0 = wd * 64;
+            up = a < c0 ? ~0ull : (a >= c0 + 63 ? 0ull : ~((2ull << (a - c0)) - 1));
+          }
+          nu += __popcll(und & up);
+          nd += __popcll(vm & ~und & up);
+        }
+      }
+      const float m = wave_max_dpp(rq);
+      if ((i & 63) == 0) red[w] = m;
+      if (i < 2) cnt[8 + i] = 0;
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    raw_barrier();
+    if (__ballot(undecided) != 0 && (opaque_tid() & 63) == 0) cnt[9] = 1;
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    raw_barrier();
+    const bool compute = !hp.rb_hi || __builtin_amdgcn_readfirstlane(cnt[9]) != 0;   // block-uniform
+    tiles += compute;
+    skipped += !compute;
+    typename G::Acc acc;
+    G::zero(acc);
+    if (compute) {
+      G::resume(pipe, lds, acc);   // ends with a barrier: the ring is free
+    } else {
+      wait_vmcnt<0>();
+      raw_barrier();
+    }
+    if (more) {
+      rq = bound(cn, buf ^ 1);
+      prepare(cn, buf ^ 1);
+      issue_stage(0);
+    }
+    const int el = opaque_tid() & 63;
+    const int l31 = el & 31, hi = el >> 5;
+    bool back = false;   // block-uniform: too many close pairs
+    if (compute) {
+      float rho = 0.f;
+#pragma unroll
+      for (int i = 0; i < G::NWAVES; ++i) rho = fmaxf(rho, red[i]);
+      const float band = (2.f * rho + rho * rho + 4e-3f) * 65536.f;
+      uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * kWavePairs;
+      const int nra = c.n - c.ti * kTile, nrb = c.n - c.tj * kTile;
+      int np = 0;
+      auto push = [&](bool hit, int row, int col) {
+        if (__ballot(hit) == 0) return;
+        hit = hit && row < nra && col < nrb && !(same_tile && row >= col);
+        const uint64_t m = __ballot(hit);
+        const int at = np + __popcll(m & lanemask_lt());
+        if (hit && at < kWavePairs) pairs[at] = static_cast<uint32_t>(row << 8 | col);
+        np += __popcll(m);
+      };
+#pragma unroll
+      for (int fm = 0; fm < G::FM; ++fm) {
+        const int abase = wm * G::WTM + 32 * fm;
+        uint32_t col[3][G::FN];
+#pragma unroll
+        for (int fn = 0; fn < G::FN; ++fn) {
+          const int bbase = wn * G::WTN + 32 * fn;
+          float mx = acc[fm][fn][0];
+#pragma unroll
+          for (int v = 1; v < 16; ++v) mx = fmaxf(mx, acc[fm][fn][v]);
+          uint32_t be = 0, bg = 0, bl = 0;   // bl: not below S2
+          float dmin = __builtin_inff();
+          // (a NaN product sets no bit of any of the three)
+          if (__ballot(!(mx < tmin - band)) != 0) {
+#pragma unroll
+            for (int v = 15; v >= 0; --v) {
+              be = shift_in_ge_band(be, acc[fm][fn][v], te, dmin);
+              bg = shift_in_ge_band(bg, acc[fm][fn][v], tg, dmin);
+              bl = shift_in_ge_band(bl, acc[fm][fn][v], tl, dmin);
+            }
+            if (__ballot(dmin < band) != 0 && np <= kWavePairs) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const float p = acc[fm][fn][v];
+                push(fminf(fabsf(p - te), fminf(fabsf(p - tg), fabsf(p - tl))) < band, abase + 4 * hi + 8 * (v >> 2) + (v & 3),
+                     bbase + l31);
+              }
+            }
+          }
+          uint32_t nan = 0;
+#pragma unroll
+          for (int v = 15; v >= 0; --v) nan = 2 * nan + (acc[fm][fn][v] != acc[fm][fn][v] ? 1u : 0u);
+          col[0][fn] = spread_col_bits(be, hi, false, l31);
+          col[1][fn] = spread_col_bits(bg, hi, false, l31);
+          col[2][fn] = spread_col_bits(~(bl | nan) & 0xFFFFu, hi, false, l31);
+#pragma unroll
+          for (int m = 0; m < 3; ++m)
+            if (hi == 0) pieces(m, true)[bbase + l31][abase >> 5] = col[m][fn];
+        }
+#pragma unroll
+        for (int m = 0; m < 3; ++m) store_row_bits(col[m][0], col[m][1], hi, l31, abase, wn * G::WTN, pieces(m, false));
+      }
+      if (el == 0) cnt[w] = np;
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      raw_barrier();
+      const int mine = cnt[el & 7];
+      back = __ballot(el < G::NWAVES && mine > kWavePairs) != 0;
+      int pre[G::NWAVES + 1];
+      pre[0] = 0;
+#pragma unroll
+      for (int i = 0; i < G::NWAVES; ++i) pre[i + 1] = back ? 0 : pre[i] + __builtin_amdgcn_readlane(mine, i);
+      const int all = pre[G::NWAVES];
+      // bf16 cosines, four pairs a wave at a time (see gram_screen_kernel)
+      const float tie = static_cast<float>(2 * sa.d + 64) * 0x1p-24f;
+      const uint32_t* lists = reinterpret_cast<const uint32_t*>(lds + kListOff);
+      const int32_t* tk = tokens(buf);
+      constexpr int NP = 4;
+      for (int i0 = w * NP; i0 < all; i0 += G::NWAVES * NP) {
+        const uint16_t *pa[NP], *pb[NP];
+        float s[NP];
+        const int it = min(i0 + (el & (NP - 1)), all - 1);
+        int at = it;
+#pragma unroll
+        for (int q = 1; q < G::NWAVES; ++q)
+          if (it >= pre[q]) at = q * kWavePairs + it - pre[q];
+        const uint32_t pr = lists[at];
+        const int ta = tk[pr >> 8], tb = tk[kTile + (pr & 255)];
+        const float ia = sa.inv_norm[ta], ib = sa.inv_norm[tb];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          pa[u] = sa.x + static_cast<size_t>(__builtin_amdgcn_readlane(ta, u)) * sa.d;
+          pb[u] = sa.x + static_cast<size_t>(__builtin_amdgcn_readlane(tb, u)) * sa.d;
+          s[u] = 0.f;
+        }
+        for (int cc = el * 8; cc < sa.d; cc += 512) {
+          Pack16 a[NP], b[NP];
+#pragma unroll
+          for (int u = 0; u < NP; ++u) {
+            a[u].u4 = *reinterpret_cast<const uint4*>(pa[u] + cc);
+            b[u].u4 = *reinterpret_cast<const uint4*>(pb[u] + cc);
+          }
+#pragma unroll
+          for (int u = 0; u < NP; ++u)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s[u] = fmaf(bf16_to_f32(a[u].h[q]), bf16_to_f32(b[u].h[q]), s[u]);
+        }
+        float dot = 0.f;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+          const float t = wave_sum_dpp(s[u]);
+          dot = (el & (NP - 1)) == u ? t : dot;
+        }
+        const float cs = dot * ia * ib;
+        if (el < NP && i0 + el < all) {
+          const int r = pr >> 8, q = pr & 255;
+          if (fabsf(cs - sa.h) < tie || fabsf(cs - hp.S1) < tie || fabsf(cs - hp.S2) < tie) cnt[8] = 1;
+          const bool is[3] = {cs >= sa.h, cs > hp.S1, cs < hp.S2};
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            uint32_t* dw = &pieces(m, false)[r][q >> 5];
+            uint32_t* tw = same_tile ? &pieces(m, false)[q][r >> 5] : &pieces(m, true)[q][r >> 5];
+            if (is[m]) {
+              atomicOr(dw, 1u << (q & 31));
+              atomicOr(tw, 1u << (r & 31));
+            } else {
+              atomicAnd(dw, ~(1u << (q & 31)));
+              atomicAnd(tw, ~(1u << (r & 31)));
+            }
+          }
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      raw_barrier();
+    }
+    if (back || __builtin_amdgcn_readfirstlane(cnt[8]) != 0) {
+      if (opaque_tid() == 0) sa.list[atomicAdd(sa.list_count, 1)] = tile;
+    } else {
+      // (a skipped tile's pieces are stale and masked out: no pair is undecided)
+      const int i = opaque_tid(), rl = i >> 1, ww = 2 * (i & 1);
+#pragma unroll
+      for (int mir = 0; mir < 2; ++mir) {
+        if (mir && same_tile) break;
+        const int row = (mir ? c.tj : c.ti) * kTile + rl, wd = 4 * (mir ? c.ti : c.tj) + ww;
+        int edges = store_hist_words(hp, bitmask, base, row, wd, c.n, c.W, &pieces(0, mir)[rl][2 * ww],
+                                          &pieces(1, mir)[rl][2 * ww], &pieces(2, mir)[rl][2 * ww]);
+        edges += __shfl_xor(edges, 1, 64);
+        if (edges && (i & 1) == 0) atomicAdd(&deg[c.lo + row], edges);
+      }
+    }
+    if (!more) break;
+    // every wave's reads of the tile's LDS state are done before the next
+    // tile overwrites it
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    raw_barrier();
+    tile = ntile;
+    c = cn;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    nu += __shfl_xor(static_cast<long long>(nu), o, 64);
+    nd += __shfl_xor(static_cast<long long>(nd), o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    if (nu) atomicAdd(&hp.stats[0], nu);
+    if (nd) atomicAdd(&hp.stats[1], nd);
+  }
+  if (threadIdx.x == 0) {
+    if (tiles) atomicAdd(&hp.stats[2], tiles);
+    if (skipped) atomicAdd(&hp.stats[3], skipped);
   }
 }
 
@@ -2482,7 +2882,7 @@ struct CondenseWs {
   int* left;                    // a position stayed undecided after the greedy rounds
   int32_t* colinfo = nullptr;   // previous positions of every slot of every position
   int* queue = nullptr;         // tile queues of the similarity kernel
-  // the fp8 screen (calls without history whose shape allows it): fp8 rows
+  // the fp8 screen (calls whose shape allows it): fp8 rows
   // (and a zero row), their error bounds, the tiles left to the bf16 pass and
   // their count
   uint8_t* x8 = nullptr;
@@ -2535,7 +2935,8 @@ CondenseWs carve_condense(Carver& c, int T, int d, int E, int k, int max_bucket,
     w.stats = c.take<unsigned long long>(4);
     w.colinfo = c.take<int32_t>(static_cast<size_t>(S) * k);
     w.queue = c.take<int>(kTileQueues);
-  } else if (gram_screen_shape(T, d, E, k)) {
+  }
+  if (gram_screen_shape(T, d, E, k)) {
     w.x8 = c.take<uint8_t>(static_cast<size_t>(T + 1) * screen_pitch(d));
     w.rowq = c.take<float4>(T);
     w.list_count = c.take<int>(1);
@@ -2590,10 +2991,12 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
   // norms from the caller when given (the gate pass already read x)
   const float* inv_norm_use = inv_norm ? inv_norm : ws.inv_norm;
   // the fp8 similarity screen: its rows are written by the norm pass
-  const bool screen = !hc && bf16 && ws.x8 && threshold > 0.f && g_gram_screen.load(std::memory_order_relaxed);
+  // (a history call without a record out keeps the bf16 kernel)
+  const bool screen = (!hc || hc->out) && bf16 && ws.x8 && threshold > 0.f &&
+                      g_gram_screen.load(std::memory_order_relaxed);
   const int norm_blocks = screen ? std::max((S + 255) / 256, (T + 4) / 4)
                                  : inv_norm ? std::max(1, (S + 255) / 256) : (T + 3) / 4;
-  const int dp = screen_pitch(d), da = screen ? screen_first_values(d, dp, threshold) : 0;
+  const int dp = screen_pitch(d), da = !screen ? 0 : hc ? dp : screen_first_values(d, dp, threshold);
   {
     const int tile = bf16 ? kTile : kTileF32;
 #define LUFFY_NORM_ARGS x, T, d, inv_norm ? const_cast<float*>(inv_norm) : ws.inv_norm, S, ws.deg, ws.state, ws.claim, \
@@ -2683,14 +3086,21 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
     hp.queue = ws.queue;
     const bool hin = hc->in != nullptr, hout = hc->out != nullptr;
 #define LUFFY_GH_ARGS d, perm_token, offsets, E, inv_norm_use, hp, ws.tile_off, ws.bm_off, ws.err, ws.bitmask, ws.deg
+#define LUFFY_GHB_ARGS LUFFY_GH_ARGS, ws.list, ws.list_count
     if (bf16) {
       const uint16_t* xb = static_cast<const uint16_t*>(x);
       const int g = persistent_grid();
       const int th = GramGemm::THREADS;
-      if (hin && hout) launch("gram", gram_hist_kernel_bf16<true, true>, g, th, 0, s, xb, LUFFY_GH_ARGS);
-      else if (hin) launch("gram", gram_hist_kernel_bf16<true, false>, g, th, 0, s, xb, LUFFY_GH_ARGS);
-      else if (hout) launch("gram", gram_hist_kernel_bf16<false, true>, g, th, 0, s, xb, LUFFY_GH_ARGS);
-      else launch("gram", gram_hist_kernel_bf16<false, false>, g, th, 0, s, xb, LUFFY_GH_ARGS);
+      if (screen) {
+        const ScreenArgs sa{ws.x8, ws.rowq, xb, inv_norm_use, d, dp, da, T, threshold, ws.list, ws.list_count};
+        launch("gram", gram_hist_screen_kernel, g, th, 0, s, sa, hp, perm_token, offsets, E, ws.tile_off, ws.bm_off,
+               ws.err, ws.bitmask, ws.deg);
+        if (hin) launch("gram_recheck", gram_hist_kernel_bf16<true, true, true>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
+        else launch("gram_recheck", gram_hist_kernel_bf16<false, true, true>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
+      } else if (hin && hout) launch("gram", gram_hist_kernel_bf16<true, true>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
+      else if (hin) launch("gram", gram_hist_kernel_bf16<true, false>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
+      else if (hout) launch("gram", gram_hist_kernel_bf16<false, true>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
+      else launch("gram", gram_hist_kernel_bf16<false, false>, g, th, 0, s, xb, LUFFY_GHB_ARGS);
     } else {
       const float* xf = static_cast<const float*>(x);
       const int g = kGramF32Blocks * persistent_grid();
@@ -2699,6 +3109,7 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
       else if (hout) launch("gram", gram_kernel_f32<true, false, true>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
       else launch("gram", gram_kernel_f32<true, false, false>, g, 256, 0, s, xf, LUFFY_GH_ARGS);
     }
+#undef LUFFY_GHB_ARGS
 #undef LUFFY_GH_ARGS
   }
   const int wave_blocks = (S + 3) / 4;
