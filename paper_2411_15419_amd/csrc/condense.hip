@@ -2658,8 +2658,9 @@ __global__ __launch_bounds__(1024) void greedy_finish_kernel(
 // leaves, so no grid round precedes it), and the representative rows by the
 // block that finishes last.  Four launches of 4 to 5 us each, whose work is a
 // few reads, become one.  Blocks hand their decisions over through agent-scope
-// atomics: every state and claim written here is one, and a block counts itself
-// done (release) after them, so the last block (acquire) reads them all.
+// atomics: every state and claim written here is one, every wave waits for its
+// own (the barrier alone does not) before its block counts itself done
+// (release), so the last block (acquire) reads them all.
 // 512 positions: 19.5 -> 7.9 us; the last block takes about 1 us per 1024
 // positions, so that 16384 would take 22.6 us.
 constexpr int kSmallSlots = 4096;
@@ -2681,6 +2682,7 @@ __global__ __launch_bounds__(1024) void greedy_small_kernel(
     greedy_finish_bucket<kSmallList>(offsets[e], offsets[e + 1] - offsets[e], bitmask + bm_off[e], deg, state, claim,
                                      list, cnt);
   }
+  __threadfence();
   __syncthreads();
   if (tid == 0)
     last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == static_cast<int>(gridDim.x) - 1;
