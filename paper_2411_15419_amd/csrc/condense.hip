@@ -923,6 +923,10 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       else zq = fmaxf(zq, f.z);
     }
     const float band = (2.f * rho + rho * rho + 4e-3f) * 65536.f;
+    // a row without a bound (gram_quant_row: all of its bounds infinite) hands its
+    // tiles back whatever their products; the first phase's threshold would be a
+    // NaN where such a row meets rows that are zero past the first da values
+    const bool bounded = rho < __builtin_inff();   // block-uniform
     uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * 2 * kWavePairs;
     float* ests = reinterpret_cast<float*>(pairs + kWavePairs);
     // appends the pairs (this lane's row and column of a 32 x 32 block) with
@@ -946,8 +950,8 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       raw_barrier();
       return __ballot(el < G::NWAVES && cnt[el & 7] > limit) != 0;
     };
-    bool full = !two;          // block-uniform: the whole tile's products are taken
-    if (two) {
+    bool full = !two || !bounded;   // block-uniform: the whole tile's products are taken
+    if (two && bounded) {
       const float thr = (sa.h - (2.f * rho1 + rho1 * rho1 + 4e-3f) - zp * zq) * 65536.f;
 #pragma unroll
       for (int fm = 0; fm < G::FM; ++fm)
@@ -1029,7 +1033,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
         }
         store_row_bits(col[0], col[1], hi, l31, abase, wn * G::WTN, dbits);
       }
-      full = any_over(kWavePairs);   // from here on: too many pairs, hand the tile back
+      full = any_over(kWavePairs) || !bounded;   // from here on: hand the tile back
       if (two && more) start(cn, buf ^ 1, 0, KA);
     }
     // the waves' lists taken as one, dealt to the waves a batch at a time
@@ -2112,7 +2116,8 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
       __builtin_amdgcn_s_waitcnt(0xC07F);
       raw_barrier();
       const int mine = cnt[el & 7];
-      back = __ballot(el < G::NWAVES && mine > kWavePairs) != 0;
+      // (so does a row without a bound, see gram_screen_kernel)
+      back = __ballot(el < G::NWAVES && mine > kWavePairs) != 0 || !(rho < __builtin_inff());
       int pre[G::NWAVES + 1];
       pre[0] = 0;
 #pragma unroll

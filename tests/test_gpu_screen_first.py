@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import luffy_gen as G
-from tests.layer_runner import run_gpu, upload
+from tests.layer_runner import fetch, make_layer, upload
 from tests.test_gpu_screen import _assert_same, _near_threshold_inputs, _run
 
 pytestmark = pytest.mark.gpu
@@ -57,3 +57,38 @@ def test_close_pairs_one_by_one(near):
     print(f"[case] near={near}", flush=True)
     dev = upload(inp)
     _assert_same(_run(inp, True, h=h, dev=dev), _run(inp, False, h=h, dev=dev))
+
+
+@pytest.mark.parametrize("tail", ["full", "zero"])
+@pytest.mark.parametrize("row", ["zero", "large", "small", "overflow", "underflow", "inf", "nan"])
+def test_odd_rows(row, tail):
+    """Rows of zeros, of large and small norms, of finite values whose squares
+    over- or underflow (no bound holds for them), and with an infinity or a NaN,
+    among ordinary rows; with `tail` zero every row is zero past the values of
+    the first phase (512 of 2048 at h = 0.9)."""
+    import copy
+    import paper_2411_15419_amd as L
+    value = {"zero": 0.0, "large": 2.0 ** 40, "small": 2.0 ** -40, "overflow": 2.0 ** 100, "underflow": 2.0 ** -100}
+    inp = G.make_inputs("c3", seed=1, weights=False, T=1100, E=1, k=1, d=2048, n_centres=200)
+    if tail == "zero":
+        inp.x[:, 512:] = 0.0
+    odd = copy.deepcopy(inp)
+    for t in (5, 700):
+        if row in value:
+            odd.x[t] *= value[row]
+        else:
+            odd.x[t, 17] = np.inf if row == "inf" else np.nan
+    print(f"[case] row={row} tail={tail}", flush=True)
+    clean, dev = upload(inp), upload(odd)
+    got = []
+    for screen in (True, False):
+        was = L.set_similarity_screen(screen)
+        try:
+            layer = make_layer(odd, dev, 0.9, norms_from_route=False)
+            layer.route(clean["x"])
+            layer.condense(dev["x"])
+            got.append(fetch(layer, with_ffn=False))
+        finally:
+            L.set_similarity_screen(was)
+    _assert_same(*got)
+    assert got[0]["degree"].max() > 0
