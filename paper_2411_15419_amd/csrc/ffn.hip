@@ -557,6 +557,9 @@ __global__ __launch_bounds__(256) void ffn_split_reduce_kernel(const int32_t* __
 //    their partial tiles through LDS in wave order.  A small product is bound
 //    by the latency of its K loop, which this divides by four, and the finer
 //    tiles fill CUs that 64 x 64 tiles would leave idle.
+// GemmF32 reads rows at 32-bit offsets; a 64 x 64 tile of the first product with
+// a row of x past them (x itself has no size limit) is taken as four of the
+// second shape, whose rows are addressed in full.
 // On 8 experts of about 172 rows (512 -> 2048 -> 512) 64 x 64 tiles of vector
 // FMA took 98 and 188 us a product, these take 51 (64 x 64) and 70 us
 // (32 x 32); on 4 experts of 16 rows (256 -> 1024 -> 256) 21 and 64 us, now
@@ -636,7 +639,15 @@ __global__ __launch_bounds__(GemmF32::THREADS, kF32Blocks) void ffn_kernel_f32(
     int e, row0, rows, n0;
     map.decode(t, E, e, row0, rows, n0);
     const float* We = W + static_cast<size_t>(e) * N * K;
-    if (map.BT == 64) {
+    bool split = map.BT == 32;   // block-uniform: 32 x 32 tiles
+    if constexpr (FIRST) {
+      if (!split) {
+        const int m = row0 + min(lane, rows - 1);
+        const long long end = (static_cast<long long>(row_index ? row_index[m] : m) + 1) * K * 4;
+        split = __ballot(end > static_cast<long long>(G::kRange)) != 0;
+      }
+    }
+    if (!split) {
       uint32_t poff[G::LP], qoff[G::LQ];
 #pragma unroll
       for (int j = 0; j < G::LP; ++j) poff[j] = static_cast<uint32_t>(n0 + G::load_row(j)) * 2u * K;
@@ -653,55 +664,61 @@ __global__ __launch_bounds__(GemmF32::THREADS, kF32Blocks) void ffn_kernel_f32(
       store_block_f32<ACT, FIRST>(acc[0][0], row0 + qr, rows - qr, n0 + G::wave_m(w) * 32, N, out);
       continue;
     }
-    // lane l: weight row n0 + l % 32, token row l % 32, K values 8 s + 4 (l / 32) .. + 3 of step s
-    const int m = row0 + min(lane & 31, rows - 1);
-    const float* pw = We + static_cast<size_t>(n0 + (lane & 31)) * K + 4 * (lane >> 5);
-    const float* pa = A + static_cast<size_t>(row_index ? row_index[m] : m) * K + 4 * (lane >> 5);
-    const int nk = K / 32;                                   // 32-value chunks
-    const int c0 = w * nk / 4, c1 = (w + 1) * nk / 4;        // this wave's
-    constexpr int D = 3;                                     // chunks in flight
-    f32x4 fw[D][4], fa[D][4];
-    auto load = [&](int c, f32x4 (&w4)[4], f32x4 (&a4)[4]) {
+    const int parts = map.BT == 32 ? 1 : 4;
+    for (int q4 = 0; q4 < parts; ++q4) {
+      const int r0 = row0 + 32 * (q4 & 1), nr = min(32, rows - 32 * (q4 & 1)), col0 = n0 + 32 * (q4 >> 1);
+      if (nr <= 0) continue;
+      // lane l: weight row col0 + l % 32, token row l % 32, K values 8 s + 4 (l / 32) .. + 3 of step s
+      const int m = r0 + min(lane & 31, nr - 1);
+      const float* pw = We + static_cast<size_t>(col0 + (lane & 31)) * K + 4 * (lane >> 5);
+      const float* pa = A + static_cast<size_t>(row_index ? row_index[m] : m) * K + 4 * (lane >> 5);
+      const int nk = K / 32;                                   // 32-value chunks
+      const int c0 = w * nk / 4, c1 = (w + 1) * nk / 4;        // this wave's
+      constexpr int D = 3;                                     // chunks in flight
+      f32x4 fw[D][4], fa[D][4];
+      auto load = [&](int c, f32x4 (&w4)[4], f32x4 (&a4)[4]) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        w4[u] = *reinterpret_cast<const f32x4*>(pw + 32 * c + 8 * u);
-        a4[u] = *reinterpret_cast<const f32x4*>(pa + 32 * c + 8 * u);
+        for (int u = 0; u < 4; ++u) {
+          w4[u] = *reinterpret_cast<const f32x4*>(pw + 32 * c + 8 * u);
+          a4[u] = *reinterpret_cast<const f32x4*>(pa + 32 * c + 8 * u);
+        }
+      };
+      f32x16 acc;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+      for (int s = 0; s < D; ++s)
+        if (c0 + s < c1) load(c0 + s, fw[s], fa[s]);
+      // unrolled by D so that the register sets are indexed statically
+      for (int c = c0; c < c1; c += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+          if (c + s >= c1) break;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc = mfma32x32x8_f32(fw[s][u], fa[s][u], acc);
+          if (c + s + D < c1) load(c + s + D, fw[s], fa[s]);
+        }
       }
-    };
-    f32x16 acc;
+      // partial tiles: value v of lane l of wave w at [w][v][l]; wave w then adds
+      // values 4w..4w+3 (columns 8w + 4 (l / 32) ..) of the four waves in order
+      float* part = reinterpret_cast<float*>(lds);
+      __syncthreads();   // the previous tile's sums are read
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+      for (int v = 0; v < 16; ++v) part[(w * 16 + v) * 64 + lane] = acc[v];
+      __syncthreads();
+      if ((lane & 31) < nr) {
+        float z[4];
 #pragma unroll
-    for (int s = 0; s < D; ++s)
-      if (c0 + s < c1) load(c0 + s, fw[s], fa[s]);
-    // unrolled by D so that the register sets are indexed statically
-    for (int c = c0; c < c1; c += D) {
-#pragma unroll
-      for (int s = 0; s < D; ++s) {
-        if (c + s >= c1) break;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = mfma32x32x8_f32(fw[s][u], fa[s][u], acc);
-        if (c + s + D < c1) load(c + s + D, fw[s], fa[s]);
+        for (int q = 0; q < 4; ++q) {
+          const float* p = part + (4 * w + q) * 64 + lane;
+          z[q] = ((p[0] + p[16 * 64]) + p[32 * 64]) + p[48 * 64];
+          if constexpr (FIRST) z[q] = act_fn<ACT>(z[q]);
+        }
+        *reinterpret_cast<float4*>(out + static_cast<size_t>(r0 + (lane & 31)) * N + col0 + 8 * w + 4 * (lane >> 5)) =
+            make_float4(z[0], z[1], z[2], z[3]);
       }
     }
-    // partial tiles: value v of lane l of wave w at [w][v][l]; wave w then adds
-    // values 4w..4w+3 (columns 8w + 4 (l / 32) ..) of the four waves in order
-    float* part = reinterpret_cast<float*>(lds);
-    __syncthreads();   // the previous tile's sums are read
-#pragma unroll
-    for (int v = 0; v < 16; ++v) part[(w * 16 + v) * 64 + lane] = acc[v];
-    __syncthreads();
-    if ((lane & 31) < rows) {
-      float z[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float* p = part + (4 * w + q) * 64 + lane;
-        z[q] = ((p[0] + p[16 * 64]) + p[32 * 64]) + p[48 * 64];
-        if constexpr (FIRST) z[q] = act_fn<ACT>(z[q]);
-      }
-      *reinterpret_cast<float4*>(out + static_cast<size_t>(row0 + (lane & 31)) * N + n0 + 8 * w + 4 * (lane >> 5)) =
-          make_float4(z[0], z[1], z[2], z[3]);
-    }
+    if (parts > 1) __syncthreads();   // the sums are read before the next tile's DMA
   }
 }
 

@@ -69,3 +69,28 @@ def test_layer_f32_sizes(T, E, k, d):
     assert_route_equal(g, o)
     assert_condense_equal(g, o)
     assert_output_close(g, o, "f32")
+
+
+def test_expert_ffn_f32_rows_past_4_gib():
+    """x of more than 4 GiB (no limit is set on it): rows at offsets that 32 bits
+    do not hold, on the tile shape that reads rows at 32-bit offsets (512 tiles
+    and more)."""
+    import torch
+    import paper_2411_15419_amd as L
+    d, d_ff, R, T = 1024, 4096, 500, (1 << 20) + 4096
+    print(f"[case] expert_ffn f32 T={T} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(0)
+    x = torch.zeros(T, d, device="cuda")
+    idx = torch.randint(0, 1 << 20, (R,), generator=gen, device="cuda")
+    idx[::7] = torch.arange(T - idx[::7].numel(), T, device="cuda")
+    x[idx] = torch.randn(R, d, generator=gen, device="cuda")
+    w1 = 0.02 * torch.randn(1, d_ff, d, generator=gen, device="cuda")
+    w2 = 0.02 * torch.randn(1, d, d_ff, generator=gen, device="cuda")
+    y = torch.empty(R, d, device="cuda")
+    ws = torch.empty(L.expert_ffn_workspace_size(R, 1, d_ff, L.LUFFY_F32), dtype=torch.uint8, device="cuda")
+    L.luffy_expert_ffn(x, idx.int(), torch.tensor([0, R], dtype=torch.int32, device="cuda"), w1, w2, "silu", R, y, ws)
+    z = x[idx].double() @ w1[0].double().t()
+    ref = (z * torch.sigmoid(z)) @ w2[0].double().t()
+    err, _ = rel_err_rows(y.double().cpu().numpy(), ref.cpu().numpy())
+    assert err.max() <= TOL["f32"], f"max row rel err {err.max():.3g}"
