@@ -2687,7 +2687,10 @@ __global__ __launch_bounds__(1024) void greedy_small_kernel(
     greedy_finish_bucket<kSmallList>(offsets[e], offsets[e + 1] - offsets[e], bitmask + bm_off[e], deg, state, claim,
                                      list, cnt);
   }
-  __threadfence();
+  // this wave's states and claims are done; the counting thread's release writes
+  // the L2 back for the whole block (a fence by every wave, which repeats that,
+  // costs a 512-token layer 3 us: 62.0 against 58.9)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0)
     last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == static_cast<int>(gridDim.x) - 1;
