@@ -736,6 +736,11 @@ struct ScreenArgs {
 
 constexpr int kWavePairs = 64;    // pairs of a wave's part of a tile that can be looked at one by one
 constexpr int kWaveFirst = 32;    // of them after the first da values
+// Tiles a block takes whole after one that went on to phase 2 (gram_screen_kernel).
+// 4 buckets of 8192 tokens, d = 2048, groups of 64: 279 us with one phase, 333 with
+// every tile in two, 301 so; 8 of 2048, d = 4096, groups of 4 (some tiles go on):
+// 102, 85 and 97; where no tile goes on there is no difference.
+constexpr int kWholeTiles = 7;
 
 // Wave-wide maximum and sum, the same in every lane: DPP rotations inside the
 // rows of 16, then the four rows read as scalars (a cross-lane shuffle through
@@ -763,6 +768,71 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
   return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
+// Accumulators of a 32 x 32 block on the diagonal that lie above it (bit v: row
+// 8 (v / 4) + v % 4 + 4 hi < column l31), so that a pair is taken once.
+__device__ __forceinline__ uint32_t above_diagonal(int l31, int hi) {
+  const int q = l31 - 4 * hi;
+  return q > 0 ? (1u << (4 * (q >> 3) + min(q & 7, 4))) - 1u : 0u;
+}
+
+// bits * 2 + (x < 0): the sign of a difference, without a compare (a NaN shifts in
+// either).
+__device__ __forceinline__ uint32_t shift_in_sign(uint32_t bits, float x) {
+  return __builtin_amdgcn_alignbit(bits, __float_as_uint(x), 31);
+}
+
+// Sum over the lanes below this one, and over the wave: DPP shifts within the
+// rows of 16, then the last lanes of rows broadcast to the rows after them.
+__device__ __forceinline__ int wave_prefix_dpp(int x, int& total) {
+  int s = x;
+  s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, true);
+  s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, true);
+  s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, true);
+  s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, true);
+  s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, true);
+  s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xC, 0xF, true);
+  total = __builtin_amdgcn_readlane(s, 63);
+  return s - x;
+}
+
+// The pairs of a wave's part of a tile (FM x 2 blocks of 32 x 32) that are looked
+// at one by one: left[fm] marks this lane's accumulators of blocks (fm, 0) and
+// (fm, 1) in its low and high half (bit v: row 8 (v / 4) + v % 4 + 4 hi, column
+// l31 of the block).  Counts the marked ones and, where they are at most `limit`,
+// lists them in LDS (row << 8 | column; the wave's first row and column of the
+// tile in row0, col0), each lane its own, so that the loops take a step for each
+// pair of the fullest lane.  (Taken value by value with a ballot each, the 32
+// pairs of a wave took 4 us.)
+template <int FM>
+__device__ __forceinline__ int list_pairs(const uint32_t (&left)[FM], int limit, int row0, int col0, uint32_t* pairs) {
+  const int lane = opaque_tid() & 63;
+  int mine = 0, total;
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm) mine += __popc(left[fm]);
+  if (__ballot(mine != 0) == 0) return 0;   // the common case
+  int at = wave_prefix_dpp(mine, total);
+  if (total > limit) return total;
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+    for (uint32_t m = left[fm]; m != 0; m &= m - 1) {
+      const int b = __ffs(static_cast<int>(m)) - 1, v = b & 15;
+      const int row = row0 + 32 * fm + 8 * (v >> 2) + (v & 3) + 4 * (lane >> 5);
+      const int col = col0 + 32 * (b >> 4) + (lane & 31);
+      pairs[at++] = static_cast<uint32_t>(row << 8 | col);
+    }
+  return total;
+}
+
+// Marks of a 32 x 32 block whose rows and columns are all taken: rows from row0 on
+// and columns from col0 on of a tile of nra x nrb, those above the diagonal on a
+// diagonal block.
+__device__ __forceinline__ uint32_t valid_marks(int row0, int col0, int nra, int nrb, bool diagonal, int l31, int hi) {
+  const int q = nra - row0 - 4 * hi;   // rows left: a prefix of the marks, as above_diagonal's
+  uint32_t m = q >= 28 ? 0xFFFFu : q > 0 ? (1u << (4 * (q >> 3) + min(q & 7, 4))) - 1u : 0u;
+  if (diagonal) m &= above_diagonal(l31, hi);
+  return col0 + l31 < nrb ? m : 0u;
+}
+
 // The similarity screen: every upper-triangle tile decided from fp8 products
 // where their error bound allows it, and from single products of two rows where
 // a few pairs of it are too close.  The result is the one of the bf16 pass.
@@ -774,9 +844,13 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
 // different meaning are nearly orthogonal, so what is left is little more than
 // the tile's edges themselves (an expert's bucket of n tokens in groups of g
 // has about 65536 (g - 1) / n of them per tile).  Each wave keeps the pairs left
-// of its part of the tile; if no wave has more than kWaveFirst, every wave adds
-// the rest of its pairs' fp8 products one pair at a time.  Otherwise phase 2
-// multiplies the rest of the values for the whole tile.  Either way a pair whose
+// of its part of the tile; if no wave has more than kWaveFirst, their fp8
+// products are taken one pair at a time.  Otherwise phase 2 multiplies the rest of
+// the values for the whole tile, and the block's next kWholeTiles tiles take all
+// values at once (a tile that goes on to phase 2 takes about 4 us longer than one
+// that does not try: the compares, a barrier, the ring's refill; tiles of one call
+// mostly go the same way).  A block without a next tile prefetches its phase 2
+// in the next tile's place.  Either way a pair whose
 // full estimate is further than band from h is decided, and a closer one gets
 // its bf16 dot product.  A tile where a wave has more than kWavePairs of those,
 // or one whose dot product is within float32 rounding of h, is listed for the
@@ -796,12 +870,12 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
   static_assert(G::BM == kTile && G::BN == kTile && G::THREADS == 2 * kTile && G::NWAVES == 8, "one row a thread");
   // one LDS array (see gram_kernel_bf16): the operand ring, the waves' row
   // bounds, the tokens of this tile and of the next (P rows, then Q rows), the
-  // adjacency pieces, the bucket tables, every wave's pairs (row << 8 | column,
-  // then their estimates so far), every wave's pairs still too close after
-  // their whole fp8 product, the pair counts and the hand-back flag
+  // adjacency pieces, the bucket tables, every wave's pairs (row << 8 | column),
+  // every wave's pairs still too close after their whole fp8 product, the pair
+  // counts and the hand-back flag
   constexpr int kRedOff = G::LDS_BYTES, kTokOff = kRedOff + G::NWAVES * 16, kBitsOff = kTokOff + 4 * kTile * 4;
   constexpr int kTabOff = kBitsOff + 2 * kTile * (kTile / 32) * 4, kListOff = kTabOff + 3 * kMaxExperts * 4;
-  constexpr int kCloseOff = kListOff + G::NWAVES * kWavePairs * 8, kCntOff = kCloseOff + G::NWAVES * kWavePairs * 4;
+  constexpr int kCloseOff = kListOff + G::NWAVES * kWavePairs * 4, kCntOff = kCloseOff + G::NWAVES * kWavePairs * 4;
   __shared__ __attribute__((aligned(16))) uint8_t lds[kCntOff + 48];
   float4* red = reinterpret_cast<float4*>(lds + kRedOff);
   uint32_t (*dbits)[kTile / 32] = reinterpret_cast<uint32_t (*)[kTile / 32]>(lds + kBitsOff);
@@ -816,7 +890,6 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
   if (tile >= total) return;   // block-uniform, before any barrier
   const uint16_t* X = reinterpret_cast<const uint16_t*>(sa.x8);
   const int K = sa.dp / 2, KA = sa.da / 2;   // 16-bit units, 64 a stage
-  const bool two = KA < K;
   if (w == 0) {
     int to, o0, o1;
     bucket_lookup_loads(tile_off, offsets, E, to, o0, o1);
@@ -877,9 +950,12 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
   fetch_tokens(c, 0);
   __syncthreads();   // (waits for the DMA too)
   float4 rq = bounds(c, 0);
-  start(c, 0, 0, KA);
+  start(c, 0, 0, K);
   const float hs = sa.h * 65536.f;   // the threshold in units of the fp8 products (exact)
+  int whole = 0;   // tiles that this block takes whole before it tries the first values again
   for (int buf = 0;; buf ^= 1) {
+    const bool two = KA < K && whole == 0;
+    pipe.nk = (two ? KA : K) / G::BK;
     const int ntile = tile + gridDim.x;
     const bool more = ntile < total;
     TileCoord cn = c;
@@ -893,8 +969,10 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       const int tid = opaque_tid();
       if ((tid & 63) == 0) red[w] = m;
       if (tid == 0) cnt[8] = 0;
-      uint4* z = reinterpret_cast<uint4*>(&dbits[0][0]);
-      z[tid] = z[tid + G::THREADS] = make_uint4(0u, 0u, 0u, 0u);
+      if (two) {   // (a whole tile's pieces are all written)
+        uint4* z = reinterpret_cast<uint4*>(&dbits[0][0]);
+        z[tid] = z[tid + G::THREADS] = make_uint4(0u, 0u, 0u, 0u);
+      }
       static_assert(2 * G::THREADS * 16 == 2 * kTile * (kTile / 32) * 4, "cleared pieces");
     }
     typename G::Acc acc;
@@ -904,11 +982,13 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       // the next tile's first stages are issued between this tile's compares
       // and land under the rest of its epilogue
       rq = bounds(cn, buf ^ 1);
-      prepare(cn, buf ^ 1, 0, KA);
+      prepare(cn, buf ^ 1, 0, K);
       if (!two) {
 #pragma unroll
         for (int i = 0; i < kDma; ++i) G::issue_one(pipe, i, lds);
       }
+    } else if (two) {
+      prepare(c, buf, KA, K - KA);   // no next tile: this one's second phase, if it comes to it
     }
     const int el = opaque_tid() & 63;
     const int l31 = el & 31, hi = el >> 5;
@@ -927,23 +1007,11 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
     // tiles back whatever their products; the first phase's threshold would be a
     // NaN where such a row meets rows that are zero past the first da values
     const bool bounded = rho < __builtin_inff();   // block-uniform
-    uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * 2 * kWavePairs;
-    float* ests = reinterpret_cast<float*>(pairs + kWavePairs);
-    // appends the pairs (this lane's row and column of a 32 x 32 block) with
-    // `hit` set: pairs of rows inside the bucket, on a diagonal tile each once
+    uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * kWavePairs;
     const int nra = c.n - c.ti * kTile, nrb = c.n - c.tj * kTile;
+    uint32_t left[G::FM] = {};   // the pairs left of this lane's part (list_pairs)
+    static_assert(G::FN == 2, "two blocks a word");
     int np = 0;
-    auto push = [&](bool hit, float est, int row, int col) {
-      if (__ballot(hit) == 0) return;
-      hit = hit && row < nra && col < nrb && !(same_tile && row >= col);
-      const uint64_t m = __ballot(hit);
-      const int at = np + __popcll(m & lanemask_lt());
-      if (hit && at < kWavePairs) {
-        pairs[at] = static_cast<uint32_t>(row << 8 | col);
-        ests[at] = est;
-      }
-      np += __popcll(m);
-    };
     auto any_over = [&](int limit) {   // block-uniform
       if (el == 0) cnt[w] = np;
       __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -958,38 +1026,35 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
 #pragma unroll
         for (int fn = 0; fn < G::FN; ++fn) {
           constexpr int PER = (kDma + G::FM * G::FN - 1) / (G::FM * G::FN);
-          if (more) {
 #pragma unroll
-            for (int i = 0; i < PER; ++i)
-              if ((fm * G::FN + fn) * PER + i < kDma) G::issue_one(pipe, (fm * G::FN + fn) * PER + i, lds);
-          }
-          // most blocks have no pair left or one: maxima of four accumulators
-          // are tested before single ones
-          float m4[4];
+          for (int i = 0; i < PER; ++i)
+            if ((fm * G::FN + fn) * PER + i < kDma) G::issue_one(pipe, (fm * G::FN + fn) * PER + i, lds);
+          const int abase = wm * G::WTM + 32 * fm, bbase = wn * G::WTN + 32 * fn;
+          if (same_tile && abase > bbase) continue;   // the mirror's pairs
+          // most blocks have no pair left: their largest value is tested first
+          float mx = acc[fm][fn][0];
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            m4[g] = fmaxf(fmaxf(acc[fm][fn][4 * g], acc[fm][fn][4 * g + 1]),
-                          fmaxf(acc[fm][fn][4 * g + 2], acc[fm][fn][4 * g + 3]));
-          if (__ballot(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])) >= thr) == 0) continue;
-          if (np > kWaveFirst) continue;   // too many already
-          const int row = wm * G::WTM + 32 * fm + 4 * hi, col = wn * G::WTN + 32 * fn + l31;
+          for (int v = 1; v < 16; ++v) mx = fmaxf(mx, acc[fm][fn][v]);
+          if (__ballot(mx >= thr) == 0) continue;
+          uint32_t hits = 0;
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (__ballot(m4[g] >= thr) == 0) continue;
-#pragma unroll
-            for (int v = 4 * g; v < 4 * g + 4; ++v)
-              push(acc[fm][fn][v] >= thr, acc[fm][fn][v], row + 8 * (v >> 2) + (v & 3), col);
-          }
+          for (int v = 15; v >= 0; --v) hits = shift_in_sign(hits, thr - acc[fm][fn][v]);
+          left[fm] |= (hits & valid_marks(abase, bbase, nra, nrb, same_tile && abase == bbase, l31, hi)) << 16 * fn;
         }
+      np = list_pairs(left, kWaveFirst, wm * G::WTM, wn * G::WTN, pairs);
       full = any_over(kWaveFirst);
       if (full) {
         // the rest of the values: the ring is taken back from the next tile
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        raw_barrier();
-        start(c, buf, KA, K - KA);
+        if (more) {
+          wait_vmcnt<0>();
+          __builtin_amdgcn_s_waitcnt(0xC07F);
+          raw_barrier();
+          start(c, buf, KA, K - KA);
+        }
+        whole = kWholeTiles + 1;
         G::resume(pipe, lds, acc);
-        np = 0;
+#pragma unroll
+        for (int fm = 0; fm < G::FM; ++fm) left[fm] = 0;
       }
     }
     const bool first_only = !full;
@@ -1023,18 +1088,20 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
 #pragma unroll
             for (int v = 15; v >= 0; --v) bits = shift_in_ge_band(bits, acc[fm][fn][v], hs, dmin);
           }
-          if (__ballot(dmin < band) != 0 && np <= kWavePairs) {
+          if (__ballot(dmin < band) != 0 && !(same_tile && abase > bbase)) {
+            uint32_t hits = 0;
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              push(fabsf(acc[fm][fn][v] - hs) < band, 0.f, abase + 4 * hi + 8 * (v >> 2) + (v & 3), bbase + l31);
+            for (int v = 15; v >= 0; --v) hits = shift_in_sign(hits, fabsf(acc[fm][fn][v] - hs) - band);
+            left[fm] |= (hits & valid_marks(abase, bbase, nra, nrb, same_tile && abase == bbase, l31, hi)) << 16 * fn;
           }
           col[fn] = spread_col_bits(bits, hi, same_tile && abase == bbase, l31);
           if (hi == 0) tbits[bbase + l31][abase >> 5] = col[fn];
         }
         store_row_bits(col[0], col[1], hi, l31, abase, wn * G::WTN, dbits);
       }
+      np = list_pairs(left, kWavePairs, wm * G::WTM, wn * G::WTN, pairs);
       full = any_over(kWavePairs) || !bounded;   // from here on: hand the tile back
-      if (two && more) start(cn, buf ^ 1, 0, KA);
+      if (two && more) start(cn, buf ^ 1, 0, K);
     }
     // the waves' lists taken as one, dealt to the waves a batch at a time
     int pre[G::NWAVES + 1];   // scalars: pairs before each wave's
@@ -1053,14 +1120,16 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       int at = i;
 #pragma unroll
       for (int q = 1; q < G::NWAVES; ++q)
-        if (i >= pre[q]) at = q * 2 * kWavePairs + i - pre[q];
+        if (i >= pre[q]) at = q * kWavePairs + i - pre[q];
       return at;
     };
     uint32_t* close = reinterpret_cast<uint32_t*>(lds + kCloseOff) + w * kWavePairs;
     int nclose = 0;
     if (first_only) {
-      // the rest of the fp8 products, eight pairs at a time; a decided edge is
-      // set, the pairs still within the band are kept for the dot product
+      // the whole fp8 products, eight pairs at a time; a decided edge is set, the
+      // pairs still within the band are kept for the dot product.  (The first da
+      // values once more: a sum kept from the accumulators would need each pair's
+      // own register.)
       const int32_t* tk = tokens(buf);
       constexpr int NP = 8;
       for (int i0 = w * NP; i0 < all; i0 += G::NWAVES * NP) {
@@ -1077,7 +1146,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
         }
         // two 1 KB pieces of every row in flight (the loads' latency, not their
         // bytes, is what a batch waits for)
-        for (int cc = sa.da + el * 16; cc < sa.dp; cc += 2048) {
+        for (int cc = el * 16; cc < sa.dp; cc += 2048) {
           uint4 a[2][NP], b[2][NP];
 #pragma unroll
           for (int h2 = 0; h2 < 2; ++h2)
@@ -1104,13 +1173,13 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
               }
             }
         }
-        float rest = 0.f;   // of pair i0 + el % NP
+        float sum = 0.f;   // of pair i0 + el % NP
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
           const float t = wave_sum_dpp(s[u]);
-          rest = (el & (NP - 1)) == u ? t : rest;
+          sum = (el & (NP - 1)) == u ? t : sum;
         }
-        const float d = reinterpret_cast<const float*>(lists)[my + kWavePairs] + rest - hs;
+        const float d = sum - hs;
         const bool mine = el < NP && i0 + el < all;
         const bool near = mine && !(fabsf(d) >= band);   // (a NaN goes on to the dot product)
         if (mine && d >= band) {
@@ -1179,14 +1248,20 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
       }
     }
     // LDS-only barriers: a full __syncthreads() would also wait for the next
-    // tile's DMA
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    raw_barrier();
+    // tile's DMA (the pieces of the products passed any_over's)
+    if (all > 0) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      raw_barrier();
+    }
     if (!full && __builtin_amdgcn_readfirstlane(cnt[8]) == 0)
       write_gram_tile(c, dbits, tbits, bitmask, bm_off[c.e], deg, G::THREADS);
     else if (opaque_tid() == 0)
       sa.list[atomicAdd(sa.list_count, 1)] = tile;
-    if (!more) break;
+    if (!more) {
+      wait_vmcnt<0>();   // a second phase's first stages that were not needed
+      break;
+    }
+    if (whole > 0) --whole;
     // every wave's reads of the tile's LDS state are done before the next
     // tile overwrites it
     __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -2061,15 +2136,8 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
       const float band = (2.f * rho + rho * rho + 4e-3f) * 65536.f;
       uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * kWavePairs;
       const int nra = c.n - c.ti * kTile, nrb = c.n - c.tj * kTile;
-      int np = 0;
-      auto push = [&](bool hit, int row, int col) {
-        if (__ballot(hit) == 0) return;
-        hit = hit && row < nra && col < nrb && !(same_tile && row >= col);
-        const uint64_t m = __ballot(hit);
-        const int at = np + __popcll(m & lanemask_lt());
-        if (hit && at < kWavePairs) pairs[at] = static_cast<uint32_t>(row << 8 | col);
-        np += __popcll(m);
-      };
+      uint32_t left[G::FM] = {};   // the close pairs of this lane's part (list_pairs)
+      static_assert(G::FN == 2, "two blocks a word");
 #pragma unroll
       for (int fm = 0; fm < G::FM; ++fm) {
         const int abase = wm * G::WTM + 32 * fm;
@@ -2090,13 +2158,14 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
               bg = shift_in_ge_band(bg, acc[fm][fn][v], tg, dmin);
               bl = shift_in_ge_band(bl, acc[fm][fn][v], tl, dmin);
             }
-            if (__ballot(dmin < band) != 0 && np <= kWavePairs) {
+            if (__ballot(dmin < band) != 0 && !(same_tile && abase > bbase)) {
+              uint32_t hits = 0;
 #pragma unroll
-              for (int v = 0; v < 16; ++v) {
+              for (int v = 15; v >= 0; --v) {
                 const float p = acc[fm][fn][v];
-                push(fminf(fabsf(p - te), fminf(fabsf(p - tg), fabsf(p - tl))) < band, abase + 4 * hi + 8 * (v >> 2) + (v & 3),
-                     bbase + l31);
+                hits = shift_in_sign(hits, fminf(fabsf(p - te), fminf(fabsf(p - tg), fabsf(p - tl))) - band);
               }
+              left[fm] |= (hits & valid_marks(abase, bbase, nra, nrb, same_tile && abase == bbase, l31, hi)) << 16 * fn;
             }
           }
           uint32_t nan = 0;
@@ -2112,6 +2181,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
 #pragma unroll
         for (int m = 0; m < 3; ++m) store_row_bits(col[m][0], col[m][1], hi, l31, abase, wn * G::WTN, pieces(m, false));
       }
+      const int np = list_pairs(left, kWavePairs, wm * G::WTM, wn * G::WTN, pairs);
       if (el == 0) cnt[w] = np;
       __builtin_amdgcn_s_waitcnt(0xC07F);
       raw_barrier();

@@ -28,6 +28,8 @@ def _need_gpu():
     (4096, 4, 2, 2048, 0.45, 512),   # a threshold whose first phase would be most of the row: one phase
     (2048, 4, 2, 4096, 0.97, 256),
     (2049, 4, 1, 8192, 0.9, 300),    # one row past a tile
+    (9000, 1, 1, 2048, 0.9, 400),    # two or three tiles a block, some of which go on
+    (17000, 1, 1, 2048, 0.9, 100),   # nine tiles a block, all of which go on: whole tiles, then a new try
 ])
 def test_phases(T, E, k, d, h, n_centres):
     inp = G.make_inputs("c3", seed=d + n_centres, weights=False, T=T, E=E, k=k, d=d, n_centres=n_centres)
