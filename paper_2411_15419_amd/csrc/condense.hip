@@ -1718,14 +1718,16 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
   // Tiles cost very different times (skipped or computed), so blocks take
   // them from queues: queue x holds the x-th eighth of the tile order, a
   // block first drains the queue of its own XCD (blocks are dealt to the
-  // XCDs round-robin), then the others'.
+  // XCDs round-robin), then the others'.  Listed tiles are all computed and are
+  // taken in turn: eight empty queues alone took 27 us.
   __shared__ int next_tile;
   const int home = blockIdx.x % kTileQueues;
   int qi = 0;
-  for (;;) {
+  for (int item = LIST ? xcd_virtual_block() : 0;; item += gridDim.x) {
     if (tid == 0) {
       int t = -1;
-      while (qi < kTileQueues) {
+      if (LIST && item < total) t = list[item];
+      while (!LIST && qi < kTileQueues) {
         const int x = (home + qi) % kTileQueues;
         const int t0 = static_cast<int>(static_cast<long long>(total) * x / kTileQueues);
         const int t1 = static_cast<int>(static_cast<long long>(total) * (x + 1) / kTileQueues);
@@ -1740,7 +1742,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_kernel_bf16(
     }
     __syncthreads();
     if (next_tile < 0) break;
-    const int tile = LIST ? list[next_tile] : next_tile;
+    const int tile = next_tile;
     const TileCoord c = decode_tile_grouped(tile, tile_off, offsets, E);
     const int32_t* pt = perm_token + c.lo;
     const long long bmo = bm_off[c.e];
@@ -1972,7 +1974,9 @@ __device__ __forceinline__ int store_hist_words(const HistParams& hp, uint64_t* 
 // threshold as a whole and need no compares.  A tile whose pairs are all
 // decided skips the product.  The tile loop is pipelined as the screen's, with
 // one stage of the next tile's operands in flight: the other stage's LDS holds
-// the pieces.
+// the pieces.  Where cosines crowd the thresholds, so that a block's tiles are
+// handed back one after the other, it hands the next ones back at once (1, 3, then
+// 7 of them) before it takes a product again.
 // Why: the bf16 kernel spent 77,000 cycles of a 256 x 256 tile of d = 2048 on
 // its K loop and as many on 3 predicates with two bit lookups a pair; fp8 halves
 // the first and the word-level merge leaves one compare a predicate.  Two
@@ -2064,6 +2068,9 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
   const float te = sa.h * 65536.f, tg = hp.S1 * 65536.f, tl = hp.S2 * 65536.f;
   const float tmin = fminf(fminf(te, tg), tl);
   unsigned long long nu = 0, nd = 0, tiles = 0, skipped = 0;
+  // computed tiles handed back in a row (1, 2, 4, .. at most 8), and the tiles to
+  // hand back without their product after them
+  int strike = 0, direct = 0;
   for (int buf = 0;; buf ^= 1) {
     const int ntile = tile + gridDim.x;
     const bool more = ntile < total;
@@ -2110,9 +2117,11 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
     if (__ballot(undecided) != 0 && (opaque_tid() & 63) == 0) cnt[9] = 1;
     __builtin_amdgcn_s_waitcnt(0xC07F);
     raw_barrier();
-    const bool compute = !hp.rb_hi || __builtin_amdgcn_readfirstlane(cnt[9]) != 0;   // block-uniform
-    tiles += compute;
-    skipped += !compute;
+    const bool left = !hp.rb_hi || __builtin_amdgcn_readfirstlane(cnt[9]) != 0;   // block-uniform
+    tiles += left;
+    skipped += !left;
+    const bool compute = left && direct == 0;
+    if (left && direct > 0) --direct;
     typename G::Acc acc;
     G::zero(acc);
     if (compute) {
@@ -2128,7 +2137,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
     }
     const int el = opaque_tid() & 63;
     const int l31 = el & 31, hi = el >> 5;
-    bool back = false;   // block-uniform: too many close pairs
+    bool back = left && !compute;   // block-uniform: too many close pairs
     if (compute) {
       float rho = 0.f;
 #pragma unroll
@@ -2136,7 +2145,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
       const float band = (2.f * rho + rho * rho + 4e-3f) * 65536.f;
       uint32_t* pairs = reinterpret_cast<uint32_t*>(lds + kListOff) + w * kWavePairs;
       const int nra = c.n - c.ti * kTile, nrb = c.n - c.tj * kTile;
-      uint32_t left[G::FM] = {};   // the close pairs of this lane's part (list_pairs)
+      uint32_t close[G::FM] = {};   // the close pairs of this lane's part (list_pairs)
       static_assert(G::FN == 2, "two blocks a word");
 #pragma unroll
       for (int fm = 0; fm < G::FM; ++fm) {
@@ -2165,7 +2174,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
                 const float p = acc[fm][fn][v];
                 hits = shift_in_sign(hits, fminf(fabsf(p - te), fminf(fabsf(p - tg), fabsf(p - tl))) - band);
               }
-              left[fm] |= (hits & valid_marks(abase, bbase, nra, nrb, same_tile && abase == bbase, l31, hi)) << 16 * fn;
+              close[fm] |= (hits & valid_marks(abase, bbase, nra, nrb, same_tile && abase == bbase, l31, hi)) << 16 * fn;
             }
           }
           uint32_t nan = 0;
@@ -2181,7 +2190,7 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
 #pragma unroll
         for (int m = 0; m < 3; ++m) store_row_bits(col[m][0], col[m][1], hi, l31, abase, wn * G::WTN, pieces(m, false));
       }
-      const int np = list_pairs(left, kWavePairs, wm * G::WTM, wn * G::WTN, pairs);
+      const int np = list_pairs(close, kWavePairs, wm * G::WTM, wn * G::WTN, pairs);
       if (el == 0) cnt[w] = np;
       __builtin_amdgcn_s_waitcnt(0xC07F);
       raw_barrier();
@@ -2255,7 +2264,12 @@ __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
       __builtin_amdgcn_s_waitcnt(0xC07F);
       raw_barrier();
     }
-    if (back || __builtin_amdgcn_readfirstlane(cnt[8]) != 0) {
+    back = back || __builtin_amdgcn_readfirstlane(cnt[8]) != 0;
+    if (compute) {
+      strike = !back ? 0 : strike ? min(2 * strike, 8) : 1;
+      direct = max(strike - 1, 0);
+    }
+    if (back) {
       if (opaque_tid() == 0) sa.list[atomicAdd(sa.list_count, 1)] = tile;
     } else {
       // (a skipped tile's pieces are stale and masked out: no pair is undecided)
