@@ -182,7 +182,8 @@ int luffy_condense(const void* x, int T, int d, int dtype,
 /* ------------------------------------------------------------------------
  * Similarity screen of luffy_condense and luffy_condense_history (bf16 calls
  * with d >= 2048, T*k >= 512*E and threshold > 0; of luffy_condense_history
- * those that leave a record).  The
+ * those that leave a record; not where threshold, S1 or S2 is closer to 0 than
+ * 0.06 + 3 / sqrt(d), among the cosines of unrelated tokens).  The
  * cosines of Sec. 5.1 are first estimated on fp8 (E4M3) copies of the rows,
  * each normalised, with a bound derived from every row's
  * quantisation error: |c~ - c| <= rho_a + rho_b + rho_a*rho_b (plus room for
@@ -202,7 +203,8 @@ int luffy_condense(const void* x, int T, int d, int dtype,
  *                              process; returns the previous setting.
  * luffy_similarity_screen_applies
  *                              1 if a luffy_condense call of this shape and
- *                              dtype would take the screen now, else 0.
+ *                              dtype would take the screen now (with a
+ *                              threshold as above), else 0.
  * ---------------------------------------------------------------------- */
 int luffy_set_similarity_screen(int on);
 int luffy_similarity_screen_applies(int T, int d, int E, int k, int dtype);

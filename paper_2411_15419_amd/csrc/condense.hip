@@ -2997,6 +2997,16 @@ bool gram_screen_shape(int T, int d, int E, int k) {
   return d >= 2048 && static_cast<long long>(T) * k >= 512ll * E &&
          static_cast<long long>(T + 1) * ((d + 127) / 128 * 128) <= 0xFFFF0000ll;
 }
+// A threshold the screen can decide most unrelated pairs against: their cosines
+// spread about 0 by 1 / sqrt(d), their estimates are off by up to about 0.06 (the
+// band of rows that fill their range evenly), and a wave's part of a tile holds
+// 8192 of them, of which 64 may fall inside the band.  Nearer to 0 every tile goes
+// back and the bf16 kernel alone is the faster one.  History, 16 buckets of 2048,
+// d = 2048 (line at 0.126), S2 = 0.10 / 0.12 / 0.13 / 0.2: with the screen 416 /
+// 350 / 219 / 195 us, without 248 each; 8 of 1024, d = 4096 (0.107), S2 = 0.10 /
+// 0.11: 293 / 133 and 132.  Plain, 4 of 2048, d = 4096, h = 0.10 / 0.12: 223 / 85
+// and 105.
+bool screen_room(int d, float t) { return fabsf(t) >= 0.06f + 3.f / sqrtf(static_cast<float>(d)); }
 // Pitch of the fp8 rows: whole 128-value stages.
 int screen_pitch(int d) { return (d + 127) / 128 * 128; }
 
@@ -3086,7 +3096,8 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
   const float* inv_norm_use = inv_norm ? inv_norm : ws.inv_norm;
   // the fp8 similarity screen: its rows are written by the norm pass
   // (a history call without a record out keeps the bf16 kernel)
-  const bool screen = (!hc || hc->out) && bf16 && ws.x8 && threshold > 0.f &&
+  const bool screen = (!hc || (hc->out && screen_room(d, hc->S1) && screen_room(d, hc->S2))) && bf16 && ws.x8 &&
+                      threshold > 0.f && screen_room(d, threshold) &&
                       g_gram_screen.load(std::memory_order_relaxed);
   const int norm_blocks = screen ? std::max((S + 255) / 256, (T + 4) / 4)
                                  : inv_norm ? std::max(1, (S + 255) / 256) : (T + 3) / 4;

@@ -112,11 +112,12 @@ def test_screen_norms_computed_by_condense():
     _assert_same(on, off)
 
 
-@pytest.mark.parametrize("h", [0.02, 0.999])
+@pytest.mark.parametrize("h", [0.02, 0.127, 0.999])
 def test_screen_extreme_thresholds(h):
-    """Thresholds at the ends of the range: near 0 the rows past a bucket
-    (zero products) and many cross-centre cosines fall inside the band, near
-    1 the same-centre cosines (about 0.9996) do, so many tiles go back to the
+    """Thresholds at the ends of the range: at 0.02 the call keeps the bf16
+    kernel, just above 0.126 (the least threshold the screen takes at
+    d = 2048) some cross-centre cosines fall inside the band, near 1 the
+    same-centre cosines (about 0.9996) do, so that many tiles go back to the
     bf16 pass; the outputs still equal the all-bf16 call bit for bit.  (The
     oracle is not compared here: at these thresholds some float64 cosines
     lie within float32 rounding of h, which is the all-bf16 path's own

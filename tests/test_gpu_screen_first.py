@@ -94,3 +94,52 @@ def test_odd_rows(row, tail):
             L.set_similarity_screen(was)
     _assert_same(*got)
     assert got[0]["degree"].max() > 0
+
+
+def _launches(kernel, call):
+    import torch
+    import paper_2411_15419_amd as L
+    L.profile_kernel(kernel)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return L.profile_read()[1]
+    finally:
+        L.profile_kernel(None)
+
+
+@pytest.mark.parametrize("h,S1,S2,screened", [
+    (0.9, 0.8, 0.2, True), (0.13, 0.8, 0.2, True), (0.9, 0.8, -0.2, True), (0.9, np.inf, -np.inf, True),
+    (0.12, 0.8, 0.2, False), (0.9, 0.8, 0.1, False), (0.9, -0.1, 0.2, False), (0.9, 0.8, 0.0, False),
+])
+def test_thresholds_among_unrelated_cosines(h, S1, S2, screened):
+    """Calls with a threshold among the cosines of unrelated tokens (within 0.06 +
+    3 / sqrt(2048) = 0.126 of 0) keep the bf16 kernels; outputs do not depend on
+    it.  Plain calls go by h alone."""
+    import paper_2411_15419_amd as L
+    inp = G.make_inputs("c3", seed=2, weights=False, T=1500, E=2, k=1, d=2048, n_centres=300)
+    dev = upload(inp)
+    plain = make_layer(inp, dev, h)
+    hist = L.MoELayer(plain.w_gate, plain.b_gate, plain.w1, plain.w2, k=1, act=inp.cfg.act, threshold=h,
+                      capacity_factor=inp.cfg.capacity_factor, T=1500, history=(S1, S2))
+    print(f"[case] h={h} S1={S1} S2={S2}", flush=True)
+    out = {}
+    for on in (True, False):
+        was = L.set_similarity_screen(on)
+        try:
+            for name, layer in (("plain", plain), ("hist", hist)):
+                layer.route(dev["x"])
+                if name == "hist":
+                    layer.record.zero_()
+                n = _launches("gram_recheck", lambda: layer.condense(dev["x"]))
+                want = on and (h >= 0.126 if name == "plain" else screened)
+                assert n == want, (name, on, n)
+                g = fetch(layer, with_ffn=False)
+                if name == "hist":
+                    g["record"] = layer.record.cpu().numpy()
+                out[name, on] = g
+        finally:
+            L.set_similarity_screen(was)
+    for name in ("plain", "hist"):
+        _assert_same(out[name, True], out[name, False])
+    assert np.array_equal(out["hist", True]["record"], out["hist", False]["record"])
