@@ -2742,19 +2742,59 @@ __global__ __launch_bounds__(1024) void greedy_finish_kernel(
                                     list, cnt);
 }
 
-// Small calls (at most kSmallSlots positions): the finishing pass of every
-// bucket (a block each, always run: it decides the chains that the first round
-// leaves, so no grid round precedes it), and the representative rows by the
-// block that finishes last.  Four launches of 4 to 5 us each, whose work is a
-// few reads, become one.  Blocks hand their decisions over through agent-scope
-// atomics: every state and claim written here is one, every wave waits for its
-// own (the barrier alone does not) before its block counts itself done
-// (release), so the last block (acquire) reads them all.
-// 512 positions: 19.5 -> 7.9 us; the last block takes about 1 us per 1024
-// positions, so that 16384 would take 22.6 us.
+// Small calls (at most kSmallSlots positions): the positions that the first round
+// leaves undecided, and the representative rows by the block that finishes last.
+// Four launches of 4 to 5 us each, whose work is mostly a few reads, become one
+// (512 positions: 19.5 -> 7.9 us; the last block takes about 1 us per 1024
+// positions, so that 16384 would take 22.6 us).
+// One block decides a bucket of up to kSmallAlone positions as greedy_finish_kernel
+// does.  The undecided positions of a larger one are dealt to several blocks, 16
+// lanes each, that revisit them as greedy_more_kernel does, and the last block
+// finishes what they leave: a graph of thousands of undecided positions with full
+// rows (a bucket of 4096 tokens with cosines around h) takes one block 140 to 490
+// us, these 26 to 84, the four launches 48 to 110; 4096 tokens in groups of 8, with
+// nothing left undecided: 8, 9 and 18 us.
+// Blocks hand their decisions over through agent-scope atomics: every state and
+// claim written here is one, every wave waits for its own (the barrier alone does
+// not) before its block counts itself done (release), so the last block (acquire)
+// reads them all.
 constexpr int kSmallSlots = 4096;
+constexpr int kSmallAlone = 1024;
 constexpr int kSmallList = 4096;   // undecided positions of a bucket listed at a time
 
+// Blocks of greedy_small_kernel for a bucket of n positions.
+__host__ __device__ __forceinline__ int small_share(int n) { return n <= kSmallAlone ? 1 : (n + 255) / 256; }
+
+// Share b of B of a bucket's undecided positions (every B-th position, whatever
+// the other blocks have decided by then): each 16-lane group revisits its own a
+// bounded number of times; cnt[1] records that one stayed undecided.
+__device__ __forceinline__ void greedy_share_bucket(int b, int B, int lo, int n, const uint64_t* __restrict__ rows,
+                                                    const int32_t* __restrict__ deg, int32_t* state,
+                                                    unsigned long long* __restrict__ claim, int* list, int* cnt) {
+  const int W = (n + 63) / 64, tid = threadIdx.x;
+  if (tid < 2) cnt[tid] = 0;
+  __syncthreads();
+  for (int i = b + B * tid; i < n; i += B * 1024)
+    if (load_flag(&state[lo + i]) == kStateUndecided) list[atomicAdd(&cnt[0], 1)] = i;
+  __syncthreads();
+  const int m = cnt[0];
+  constexpr int kGroups = 1024 / kVisitLanes;
+  bool still = false;
+  for (int pass = 0; pass < kGreedyPasses; ++pass) {
+    if (pass > 0) __builtin_amdgcn_s_sleep(32);
+    still = false;
+    for (int idx = tid / kVisitLanes; idx < m; idx += kGroups) {
+      const int pl = list[idx];
+      if (load_flag(&state[lo + pl]) == kStateUndecided)
+        still |= greedy_visit<true, kVisitLanes>(lo + pl, lo, n, W, rows + static_cast<long long>(pl) * W, deg, state, claim);
+    }
+    if (!still) break;
+  }
+  if (still) cnt[1] = 1;
+}
+
+// SHARED: block y of bucket x has share y of it; blocks past the bucket's do nothing.
+template <bool SHARED>
 __global__ __launch_bounds__(1024) void greedy_small_kernel(
     const int32_t* __restrict__ offsets, int E, const long long* __restrict__ bm_off, const int* __restrict__ err,
     const uint64_t* __restrict__ bitmask, const int32_t* __restrict__ deg, int32_t* state,
@@ -2763,23 +2803,52 @@ __global__ __launch_bounds__(1024) void greedy_small_kernel(
     int32_t* __restrict__ rep_offsets) {
   __shared__ __attribute__((aligned(16))) int list[2][kSmallList];
   __shared__ int cnt[2], wsum[kSmallSlots / 64 / 64];
-  __shared__ bool last;
+  __shared__ bool last, rest;
   const int failed = *err;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (!failed) {
-    const int e = blockIdx.x;
+  auto finish = [&](int e) {
     greedy_finish_bucket<kSmallList>(offsets[e], offsets[e + 1] - offsets[e], bitmask + bm_off[e], deg, state, claim,
                                      list, cnt);
+  };
+  const int e = blockIdx.x;
+  bool shared = false;   // block-uniform
+  int blocks = E;        // that count themselves done
+  if constexpr (SHARED) {
+    // (a bucket larger than max_bucket, a layout error, has the whole grid column)
+    auto of_bucket = [&](int n) { return min(small_share(n), static_cast<int>(gridDim.y)); };
+    const int n = offsets[e + 1] - offsets[e], of = of_bucket(n);
+    if (static_cast<int>(blockIdx.y) >= of) return;
+    if (wv == 0) {
+      int all;
+      wave_prefix_dpp(lane < E ? of_bucket(offsets[lane + 1] - offsets[lane]) : 0, all);
+      blocks = all;
+    }
+    shared = of > 1 && !failed;
+    if (shared)
+      greedy_share_bucket(blockIdx.y, of, offsets[e], n, bitmask + bm_off[e], deg, state, claim, &list[0][0], cnt);
   }
+  if (!shared && !failed) finish(e);
   // this wave's states and claims are done; the counting thread's release writes
   // the L2 back for the whole block (a fence by every wave, which repeats that,
   // costs a 512-token layer 3 us: 62.0 against 58.9)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (tid == 0)
-    last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == static_cast<int>(gridDim.x) - 1;
+  if (tid == 0) {
+    // low half: blocks done; high half: those that left a position undecided
+    int mine = 1;
+    if (shared && cnt[1]) mine = 0x10001;
+    const int sum = mine + __hip_atomic_fetch_add(done, mine, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    last = (sum & 0xFFFF) == blocks;
+    rest = (sum >> 16) != 0;
+  }
   __syncthreads();
   if (!last) return;
+  if (SHARED && rest) {   // block-uniform
+    for (int i = 0; i < E; ++i) {
+      finish(i);
+      __syncthreads();
+    }
+  }
   // representatives (bit p % 64 of word p / 64) and their exclusive counts
   uint64_t* mask = reinterpret_cast<uint64_t*>(&list[0][0]);
   int* pre = &list[1][0];
@@ -2806,7 +2875,7 @@ __global__ __launch_bounds__(1024) void greedy_small_kernel(
     if (p < S) rep_of_pos[p] = q[i];
   }
   __syncthreads();
-  // exclusive prefix of the words' counts, a word a thread (at most 256 words)
+  // exclusive prefix of the words' counts, a word a thread (one wave)
   const int words = (S + 63) / 64;
   int own = 0, incl = 0;
   if (tid < kSmallSlots / 64) {
@@ -2973,7 +3042,8 @@ struct CondenseWs {
   uint64_t* rb_hi = nullptr;
   uint64_t* rb_lo = nullptr;
   unsigned long long* stats = nullptr;
-  int* left;                    // a position stayed undecided after the greedy rounds
+  int* left;                    // a position stayed undecided after the greedy rounds (small calls: the
+                                // finished blocks of greedy_small_kernel)
   int32_t* colinfo = nullptr;   // previous positions of every slot of every position
   int* queue = nullptr;         // tile queues of the similarity kernel
   // the fp8 screen (calls whose shape allows it): fp8 rows
@@ -3222,8 +3292,12 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
   launch("greedy_round", greedy_round_kernel, visit_blocks, 256, 0, s, offsets, E, ws.bm_off, ws.err, ws.bitmask,
          ws.deg, ws.state, ws.claim, degree);
   if (S <= kSmallSlots) {   // see greedy_small_kernel
-    launch("greedy_finish", greedy_small_kernel, E, 1024, 0, s, offsets, E, ws.bm_off, ws.err, ws.bitmask, ws.deg,
-           ws.state, ws.claim, ws.left, perm_token, rep_of_pos, rep_row, rep_token, rep_offsets);
+#define LUFFY_SMALL_ARGS offsets, E, ws.bm_off, ws.err, ws.bitmask, ws.deg, ws.state, ws.claim, ws.left, perm_token, \
+                         rep_of_pos, rep_row, rep_token, rep_offsets
+    const int share = small_share(std::min(S, max_bucket));
+    if (share == 1) launch("greedy_finish", greedy_small_kernel<false>, E, 1024, 0, s, LUFFY_SMALL_ARGS);
+    else launch("greedy_finish", greedy_small_kernel<true>, dim3(E, share), 1024, 0, s, LUFFY_SMALL_ARGS);
+#undef LUFFY_SMALL_ARGS
   } else {
     launch("greedy_more", greedy_more_kernel, std::min(visit_blocks, persistent_grid()), 256, 0, s, offsets, E,
            ws.bm_off, ws.err, ws.bitmask, ws.deg, ws.state, ws.claim, ws.left);
