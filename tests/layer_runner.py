@@ -129,3 +129,42 @@ def assert_output_close(g, o, dtype):
     dropped = (o.slot_pos < 0).all(axis=1)
     assert np.all(g["y"][dropped] == 0), "fully dropped tokens must be zero"
     return float(err.max()) if err.size else 0.0
+
+
+def screen_state(layer):
+    """What the similarity screen's last call on `layer` left in its workspace
+    (sections in the order the library lays them out, each at a multiple of 256
+    bytes): the number of tiles, the tiles handed back to the bf16 pass, the fp8
+    rows [T, pitch] and their bounds [T, 3] (error, error of the first values,
+    share beyond them)."""
+    import torch
+    T, d, E, k, mb = layer.T, layer.d, layer.E, layer.k, layer.max_bucket
+    S, pitch = T * k, (d + 127) // 128 * 128
+    cap = S * ((mb + 63) // 64)
+    at, where = 0, {}
+    sections = [("inv_norm", 4 * T), ("tile_off", 4 * (E + 1)), ("bm_off", 8 * (E + 1)), ("err", 4), ("deg", 4 * S),
+                ("state", 4 * S), ("claim", 8 * S), ("local", 4 * S), ("bsum", 4 * ((S + 1023) // 1024 + 1)),
+                ("left", 4), ("bitmask", 8 * cap)]
+    if layer.history:
+        sections += [("rb_hi", 8 * cap), ("rb_lo", 8 * cap), ("stats", 32), ("colinfo", 4 * S * k), ("queue", 32)]
+    sections += [("x8", (T + 1) * pitch), ("rowq", 16 * T), ("list_count", 4), ("list", 0)]
+    for name, size in sections:
+        at = (at + 255) // 256 * 256
+        where[name] = (at, size)
+        at += size
+    ws = layer.buf.ws_condense
+
+    def get(name, dtype, count=None):
+        off, size = where[name]
+        size = size if count is None else count * torch.empty(0, dtype=dtype).element_size()
+        return ws[off:off + size].view(dtype)
+
+    total = int(get("tile_off", torch.int32)[E])
+    listed = get("list", torch.int32, int(get("list_count", torch.int32)[0])).cpu().numpy()
+    n = np.diff(layer.buf.offsets.cpu().numpy())
+    t = (n + 255) // 256
+    assert total == int((t * (t + 1) // 2).sum()), "workspace layout"
+    assert np.unique(listed).size == listed.size and ((listed >= 0) & (listed < total)).all(), "workspace layout"
+    rowq = get("rowq", torch.float32).view(T, 4)
+    assert bool((rowq[:, 3] == 0).all()), "workspace layout"
+    return dict(total=total, listed=listed, x8=get("x8", torch.uint8)[:T * pitch].view(T, pitch), rowq=rowq[:, :3])

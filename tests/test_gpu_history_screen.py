@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import luffy_gen as G
-from tests.layer_runner import fetch, make_layer, upload
+from tests.layer_runner import fetch, make_layer, screen_state, upload
 from tests.test_gpu_history import run_stack
 
 pytestmark = pytest.mark.gpu
@@ -23,11 +23,13 @@ def _need_gpu():
     L.load_library()
 
 
-def _chain(stack, h, S1, S2, screen, routed=None):
-    """Blocks of a stack; routed: the inputs they are routed on, if others."""
+def _chain(stack, h, S1, S2, screen, routed=None, back=None):
+    """Blocks of a stack; routed: the inputs they are routed on, if others; back
+    receives each block's tiles handed back and tiles in all."""
     import torch
     import paper_2411_15419_amd as L
     prev, out = None, []
+    back = [] if back is None else back
     was = L.set_similarity_screen(screen)
     try:
         for inp, first in zip(stack, routed or stack):
@@ -45,6 +47,9 @@ def _chain(stack, h, S1, S2, screen, routed=None):
             g = fetch(layer, with_ffn=False)
             out.append({**{n: np.array(g[n]) for n in ("offsets", "rep_offsets", "rep_of_pos", "rep_row", "degree")},
                         "stats": layer.hist_stats.cpu().numpy(), "record": layer.record.cpu().numpy()})
+            if screen:
+                state = screen_state(layer)
+                back.append((state["listed"].size, state["total"]))
             prev = layer.record
     finally:
         L.set_similarity_screen(was)
@@ -61,21 +66,30 @@ def _same(a, b):
         assert 0 < r <= n
 
 
-@pytest.mark.parametrize("T,E,k,d,h,S1,S2,centres,mix,drift", [
-    (3000, 4, 2, 2112, 0.9, 0.8, 0.2, 300, 0.05, 0.1),     # rows padded to 2176 values; ragged buckets
-    (2049, 4, 1, 2048, 0.9, 0.8, 0.2, 200, 0.5, 0.3),      # mixtures: pairs near every threshold
-    (2600, 2, 1, 2048, 0.45, 0.8, 0.2, 60, 1.0, 0.3),      # too many of them: tiles handed back
-    (2048, 4, 2, 4096, 0.97, 0.97, 0.97, 256, 0.1, 0.0),   # equal thresholds
-    (1536, 3, 2, 2048, 0.9, 2.0, -2.0, 64, 0.1, 0.1),      # nothing is decided
-    (1536, 3, 2, 2048, 0.9, -2.0, 2.0, 64, 0.1, 0.1),      # every shared pair is decided
-    (1100, 2, 1, 2048, 0.9, np.inf, -np.inf, 64, 0.1, 0.1),
-    (1025, 2, 1, 2048, 0.9, 0.8, 0.3, 16, 0.0, 0.0),       # identical blocks: every tile skipped
+# back: tiles handed back in the first and in each later block (none, some or
+# nearly all); skips: the last block skips tiles
+@pytest.mark.parametrize("T,E,k,d,h,S1,S2,centres,mix,drift,back,skips", [
+    (3000, 4, 2, 2112, 0.9, 0.8, 0.2, 300, 0.05, 0.1, ("none", "none"), False),   # rows padded to 2176 values; ragged buckets
+    (2049, 4, 1, 2048, 0.9, 0.8, 0.2, 200, 0.5, 0.3, ("none", "none"), False),    # mixtures, no pair within the band
+    (2049, 4, 1, 2048, 0.9, 0.72, 0.2, 200, 0.03, 0.3, ("none", "none", "some"), True),   # a few pairs of a tile at S1: one by one
+    (2600, 2, 1, 2048, 0.45, 0.8, 0.2, 60, 1.0, 0.3, ("all", "all"), False),      # too many of them: tiles handed back
+    (12000, 1, 1, 2048, 0.45, 0.8, 0.2, 60, 1.0, 0.3, ("all", "all"), False),     # four tiles a block, later ones without their product
+    (2048, 4, 2, 4096, 0.97, 0.97, 0.97, 256, 0.1, 0.0, ("some", "none"), True),  # equal thresholds
+    (1536, 3, 2, 2048, 0.9, 2.0, -2.0, 64, 0.1, 0.1, ("none", "none"), False),    # nothing is decided
+    (1536, 3, 2, 2048, 0.9, -2.0, 2.0, 64, 0.1, 0.1, ("none", "none"), True),     # every shared pair is decided
+    (1100, 2, 1, 2048, 0.9, np.inf, -np.inf, 64, 0.1, 0.1, ("none", "none"), False),
+    (1025, 2, 1, 2048, 0.9, 0.8, 0.3, 16, 0.0, 0.0, ("none", "none"), True),      # identical blocks: every tile skipped
 ])
-def test_forms(T, E, k, d, h, S1, S2, centres, mix, drift):
+def test_forms(T, E, k, d, h, S1, S2, centres, mix, drift, back, skips):
     stack = G.make_stack("c2", 3, seed=T + d, T=T, d=d, E=E, k=k, n_centres=centres, mix_fraction=mix,
                          capacity_factor=0.0, token_drift=drift, gate_drift=drift / 4)
     print(f"[case] T={T} E={E} k={k} d={d} h={h} S1={S1} S2={S2} mix={mix} drift={drift}", flush=True)
-    _same(_chain(stack, h, S1, S2, True), _chain(stack, h, S1, S2, False))
+    tiles = []
+    on = _chain(stack, h, S1, S2, True, back=tiles)
+    _same(on, _chain(stack, h, S1, S2, False))
+    how = ["none" if n == 0 else "all" if n > 0.9 * total else "some" for n, total in tiles]
+    assert how == [back[0], back[1], back[-1]], tiles
+    assert on[0]["stats"][3] == 0 and (on[2]["stats"][3] > 0) == skips
 
 
 @pytest.mark.parametrize("row", ["zero", "large", "small", "overflow", "underflow", "inf", "nan"])
@@ -93,7 +107,10 @@ def test_odd_rows(row):
             else:
                 inp.x[t, 17] = np.inf if row == "inf" else np.nan
     print(f"[case] row={row}", flush=True)
-    _same(_chain(stack, 0.9, 0.8, 0.3, True, routed), _chain(stack, 0.9, 0.8, 0.3, False, routed))
+    tiles = []
+    _same(_chain(stack, 0.9, 0.8, 0.3, True, routed, tiles), _chain(stack, 0.9, 0.8, 0.3, False, routed))
+    # no bound holds for rows whose squares over- or underflow: their tiles go back
+    assert [0 < n < total for n, total in tiles] == [row in ("overflow", "underflow")] * 2, tiles
 
 
 def test_oracle():
