@@ -45,6 +45,16 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+def screen_first_values(d, h):
+    """Values of a row that the similarity screen's first phase multiplies
+    (csrc/condense.hip's rule of the same name)."""
+    for da in range(128, d // 2 + 1, 128):
+        f = da / d
+        if h - (1.0 - f) >= 0.02 + 0.05 * f ** 0.5 + 6.0 * (f / d) ** 0.5:
+            return da
+    return (d + 127) // 128 * 128
+
+
 def kernel_work(name, cfg, counts, norms_from_route=True):
     """Work of one launch of a kernel: flops, the algorithmic HBM bytes of the
     measurement plan ("bytes": the FFN counts only its weights, d*d_ff*b per
@@ -60,9 +70,13 @@ def kernel_work(name, cfg, counts, norms_from_route=True):
                     bytes_act=float(nbytes if nbytes_act is None else nbytes_act))
 
     if name == "gram":
-        # on the fp8 screen the rows it streams are fp8 (one byte a value)
+        # on the fp8 screen the rows are fp8 (one byte a value) and most tiles
+        # multiply the first values only; the rest of the values of the tiles that
+        # go on and of single pairs is not counted, so the rate is a lower bound
         n = counts["bucket_sizes"]
-        return w(2.0 * d * sum(x * (x + 1) / 2 for x in n), S * d * (1 if counts.get("screen") else b))
+        screen = bool(counts.get("screen"))
+        values = screen_first_values(d, counts["threshold"]) if screen else d
+        return w(2.0 * values * sum(x * (x + 1) / 2 for x in n), S * values * (1 if screen else b))
 
     if name in ("ffn1", "ffn2"):
         wb = used * d * dff * b
@@ -73,9 +87,9 @@ def kernel_work(name, cfg, counts, norms_from_route=True):
         # with the norms from the gate pass it only clears the per-position
         # state (degree, walk state, claim key: 16 bytes a position); with the
         # fp8 similarity screen it also reads the rows and writes their fp8
-        # copies and quantisation errors
+        # copies and error bounds (16 bytes a row)
         screen = bool(counts.get("screen"))
-        nbytes = 16 * S + (T * d * b if screen or not norms_from_route else 0) + (T * d + 4 * T if screen else 0)
+        nbytes = 16 * S + (T * d * b if screen or not norms_from_route else 0) + (T * d + 16 * T if screen else 0)
         return w(0.0 if norms_from_route else 2.0 * T * d, nbytes)
     if name == "combine":
         return w(2.0 * S * d, R * d * b + 8 * T * k + T * d * b, R * d * b + 12 * T * k + T * d * b)
@@ -383,6 +397,7 @@ def measure_forward(name, thresholds, args, torch, np, G, L, with_cpu):
         ro = b.rep_offsets.cpu().numpy()
         counts = dict(S=int(off[-1]), R=int(ro[-1]), bucket_sizes=np.diff(off).tolist(),
                       used_experts=int((np.diff(ro) > 0).sum()),
+                      threshold=h,
                       screen=L.similarity_screen_applies(cfg.T, cfg.d, cfg.E, cfg.k,
                                                          L.LUFFY_BF16 if cfg.dtype == "bf16" else L.LUFFY_F32))
         rl = roofline(dominant, cfg, counts, dom_ms / dom_n / 1e3)
