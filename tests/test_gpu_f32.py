@@ -7,8 +7,8 @@ import pytest
 
 import luffy_gen as G
 from oracle import luffy_oracle as O
-from tests.layer_runner import (TOL, assert_condense_equal, assert_output_close, assert_route_equal, rel_err_rows,
-                                run_gpu, run_oracle)
+from tests.layer_runner import (TOL, assert_condense_equal, assert_output_close, assert_route_equal, fetch,
+                                rel_err_rows, run_gpu, run_oracle)
 
 pytestmark = pytest.mark.gpu
 
@@ -27,7 +27,7 @@ EDGES = [0, 1, 31, 32, 33, 63, 64, 65, 0, 200]
 # second splits K over the waves in 32 x 32 tiles; (64, 64): two K chunks for
 # four waves; (192, 4160): chunk counts that four does not divide
 @pytest.mark.parametrize("d,d_ff,act,offset", [(64, 64, "gelu", 0), (192, 4160, "silu", 0), (512, 8192, "gelu", 0),
-                                               (256, 1024, "silu", 1)])
+                                               (256, 1024, "silu", 1), (512, 8192, "gelu", 1)])
 def test_expert_ffn_f32_tiles(d, d_ff, act, offset):
     """Expert sizes around both tile edges, rows through a row index; with
     `offset` every operand starts 4 bytes past a 16-byte boundary."""
@@ -69,6 +69,32 @@ def test_layer_f32_sizes(T, E, k, d):
     assert_route_equal(g, o)
     assert_condense_equal(g, o)
     assert_output_close(g, o, "f32")
+
+
+@pytest.mark.parametrize("T,E,k,d", [(130, 2, 1, 192), (1000, 5, 2, 128), (8200, 16, 1, 64)])
+def test_layer_f32_unaligned(T, E, k, d):
+    """Tokens, gate and expert weights that start 4, 8 and 12 bytes past a 16-byte
+    boundary: the gate's vector loads and the similarity tiles' 16-byte DMA."""
+    import torch
+    import paper_2411_15419_amd as L
+    inp = G.make_inputs("c1", seed=T + 1, T=T, E=E, k=k, d=d, d_ff=128, n_centres=max(1, T // 6))
+    print(f"[case] layer f32 unaligned T={T} E={E} k={k} d={d}", flush=True)
+
+    def dev(a, offset):
+        buf = torch.zeros(a.size + offset, dtype=torch.float32, device="cuda")
+        buf[offset:] = torch.from_numpy(a.astype(np.float32).reshape(-1)).cuda()
+        return buf[offset:].view(a.shape)
+
+    o = run_oracle(inp)
+    for offset in (1, 2, 3):
+        x = dev(inp.x, offset)
+        layer = L.MoELayer(dev(inp.w_g, offset), dev(inp.b_g, 1), dev(inp.w1, offset), dev(inp.w2, offset), k=k,
+                           act=inp.cfg.act, threshold=inp.cfg.h, capacity_factor=inp.cfg.capacity_factor, T=T)
+        layer(x)
+        g = fetch(layer)
+        assert_route_equal(g, o)
+        assert_condense_equal(g, o)
+        assert_output_close(g, o, "f32")
 
 
 def test_expert_ffn_f32_rows_past_4_gib():
