@@ -32,7 +32,8 @@
 //                        when the pass before left a position undecided).
 //   rep_local_kernel, rep_finalize_kernel  representative rows by a two-pass
 //                        scan: rep_row, rep_token, rep_offsets.
-//   greedy_small_kernel  (at most 4096 slots) the last four in one launch.
+//   greedy_small_kernel  (at most 4096 slots) the last four in one launch, after
+//                        the first round.
 //   gather_kernel        optional copy of the representative rows.
 //
 // The walk of Sec. 5.2 visits positions by priority (degree descending,
@@ -858,10 +859,12 @@ __device__ __forceinline__ uint32_t valid_marks(int row0, int col0, int nra, int
 //
 // Why: a whole fp8 tile is bound by its K loop (LDS traffic and MFMA issue,
 // 2,670 cycles per 128 values) and the compares of its 65536 results; the first
-// 512 of 2048 values leave about 55 pairs of a tile of the expert-parallel
+// 512 of 2048 values leave about 60 pairs of a tile of the expert-parallel
 // share (T = 32768, d = 2048, h = 0.9).
-// That layer's similarity: whole fp8 products 519 us, this 328; 16384 i.i.d.
-// tokens of d = 4096: 111 -> 46 us.
+// That layer's similarity: whole fp8 products 519 us, this 328 (361 under the
+// profiler); 16384 i.i.d. tokens of d = 4096: 103-111 -> 37-46 us.  Calls with about
+// one tile a block whose tiles all go on lose 4 us against one phase (T = 4096, 8
+// buckets, d = 2048, groups of 4 and more: 30 -> 34).
 __global__ __launch_bounds__(GramGemm::THREADS) void gram_screen_kernel(
     ScreenArgs sa, const int32_t* __restrict__ perm_token, const int32_t* __restrict__ offsets, int E,
     const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off, const int* __restrict__ err,
@@ -1490,8 +1493,8 @@ __global__ __launch_bounds__(256) void hist_gather_kernel(const int32_t* __restr
   }
 }
 
-// The same gather for buckets whose previous rows fit in LDS: the block's 8
-// rows' previous rows (both slots) are copied to LDS once, coalesced, hi and lo
+// The same gather for buckets whose previous rows fit in LDS: the previous rows
+// (both slots) of the block's G rows (8, or 4 where buckets may be large) are copied to LDS once, coalesced, hi and lo
 // words side by side, and a lane (column) then takes both class bits of its
 // previous position with one 8-byte LDS read.  The columns of a word keep their
 // order from block to block, so most of a wave's reads fall on two or three
@@ -1505,8 +1508,9 @@ __global__ __launch_bounds__(256) void hist_gather_kernel(const int32_t* __restr
 // row and 64 columns (with a row's words in memory and 64-bit addresses about
 // 60, and one-lane stores), and by a block's chain of loads before it starts,
 // which the other block of the CU hides.  65536 slots in 32 buckets of up to
-// 19,400: 1005 -> 360 us (one block a CU 423, its rows copied one after the
-// other 620); 16384 in 16 of at most 1280: 53 -> 25 us.
+// 19,400, bound of 32768 (4 rows a block): 1005 -> 350-360 us (one block a CU 423,
+// its rows copied one after the other 620); 16384 in 16 of at most 1280 (8 rows):
+// 53 -> 25 us.
 constexpr uint32_t kNoBucket = 0xC0000000u;   // matches no position
 constexpr size_t kGatherLdsMax = 76 * 1024;   // two blocks in a CU's 160 KB
 
@@ -1586,7 +1590,7 @@ __global__ __launch_bounds__(1024) void hist_gather_lds_kernel(const int32_t* __
       P[i][j] = v >= 0 ? static_cast<uint32_t>(v) & 0xFF000000u : kNoBucket;
     }
   __syncthreads();
-  // the lane that stores: row lane % 8 of class hi (lanes 0-7) or lo (8-15)
+  // the lane that stores: row lane % G of class hi (lanes 0 .. G - 1) or lo (G .. 2 G - 1)
   const bool store = lane < 2 * G && (lane & (G - 1)) < rows;
   uint64_t* dst = (lane < G ? rb_hi : rb_lo) + bm_off[e] + static_cast<long long>(a0 + (lane & (G - 1))) * W;
   // two words (128 columns) a wave and pass: 16 bytes a storing lane
@@ -1979,9 +1983,9 @@ __device__ __forceinline__ int store_hist_words(const HistParams& hp, uint64_t* 
 // 7 of them) before it takes a product again.
 // Why: the bf16 kernel spent 77,000 cycles of a 256 x 256 tile of d = 2048 on
 // its K loop and as many on 3 predicates with two bit lookups a pair; fp8 halves
-// the first and the word-level merge leaves one compare a predicate.  Two
-// blocks of T = 32768, d = 2048, E = 32 (Zipf): 1390 -> 640 us a block, of which
-// 28 in the bf16 pass over what is handed back and 32 in the fp8 rows.
+// the first and the word-level merge leaves one compare a predicate.  A later
+// block of T = 32768, d = 2048, E = 32 (Zipf): 1405 -> 700 us, and 34 for the fp8
+// rows and 6 for the bf16 pass, which nothing goes back to.
 __global__ __launch_bounds__(GramGemm::THREADS) void gram_hist_screen_kernel(
     ScreenArgs sa, HistParams hp, const int32_t* __restrict__ perm_token, const int32_t* __restrict__ offsets, int E,
     const int32_t* __restrict__ tile_off, const long long* __restrict__ bm_off, const int* __restrict__ err,
@@ -3218,7 +3222,7 @@ void condense_enqueue(const void* x, int T, int d, int dtype, const int32_t* per
       const int cblocks = std::max(1, std::min(1024, (S + 255) / 256));
       // the rows in LDS where they fit a CU: 8 rows a block by four waves while
       // four blocks fit, 8 by 16 waves while two do, else 4 by 16 waves (buckets
-      // of up to 36,000 tokens at k = 2 then still give a CU two blocks, whose
+      // of up to 38,848 tokens at k = 2 then still give a CU two blocks, whose
       // row copies and lookups overlap); larger buckets read the rows from memory
       const size_t row_lds = hist_row_bytes(max_bucket);
       const int row_bytes = static_cast<int>(row_lds);
